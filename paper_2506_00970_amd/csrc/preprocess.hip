@@ -50,7 +50,10 @@ __device__ inline uint32_t preprocess_item(const ViewDesc* __restrict__ views, i
   const CamF cam = V.cam;
   const int n = V.n;
   const int i = item - V.item_base;  // surfel index within the view
-  if (i < 12 && saved_pose) saved_pose[v * 12 + i] = pose[i];
+  // the first items keep the pose for the backward (several entries each when the view
+  // has fewer than 12)
+  if (saved_pose)
+    for (int j = i; j < 12; j += n) saved_pose[v * 12 + j] = pose[j];
   double R[9], t[3];
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
