@@ -178,7 +178,7 @@ int ensure_pixels(gs2d_ctx* ctx, int64_t hw) {
 int ensure_tiles(gs2d_ctx* ctx, int64_t tiles) {
   if (tiles <= ctx->tile_cap) return GS2D_OK;
   GS2D_TRY(realloc_dev(ctx, &ctx->ranges, tiles));
-  GS2D_TRY(realloc_dev(ctx, &ctx->queue, kQueueOrder + tiles));
+  GS2D_TRY(realloc_dev(ctx, &ctx->order, tiles));
   ctx->tile_cap = tiles;
   return GS2D_OK;
 }
@@ -279,11 +279,11 @@ int tile_stride(int64_t n) {
   return s;
 }
 
-BlendArgs blend_args(gs2d_ctx* ctx) {
-  BlendArgs a{ctx->ranges, ctx->pval[ctx->pair_buf], ctx->rec, ctx->views, ctx->last_views.n_views,
-              (int)ctx->last_views.tiles, ctx->opt.z_near, ctx->opt.filter, ctx->opt.batch};
-  a.tile_stride = tile_stride(ctx->last_views.tiles);
-  a.queue = ctx->queue_on ? ctx->queue : nullptr;
+BlendArgs blend_args(gs2d_ctx* ctx, const ViewSet& vs, int pair_buf) {
+  BlendArgs a{ctx->ranges, ctx->pval[pair_buf], ctx->rec, ctx->views, vs.n_views,
+              (int)vs.tiles, ctx->opt.z_near, ctx->opt.filter, ctx->opt.batch};
+  a.tile_stride = tile_stride(vs.tiles);
+  a.order = ctx->order_on ? ctx->order : nullptr;
   a.check = &ctx->ctrl->check_bits;
   return a;
 }
@@ -341,7 +341,7 @@ int render_views(gs2d_ctx* ctx, const ViewSet& vs, hipStream_t s, bool allow_syn
     launch_fill_u32(ctx->last, 0u, vs.pixels, s);
     launch_fill_u32(reinterpret_cast<uint32_t*>(ctx->ranges), 0u, 2 * vs.tiles, s);
     launch_fill_u32(reinterpret_cast<uint32_t*>(ctx->ctrl), 0u, 3, s);
-    ctx->queue_on = false;
+    ctx->order_on = false;
   } else {
     clear_fresh_hist(ctx, s);
     SortPlanes ws = sort_planes(ctx);
@@ -423,15 +423,10 @@ int render_views(gs2d_ctx* ctx, const ViewSet& vs, hipStream_t s, bool allow_syn
       launch_tile_order(ctx->ranges, (int)vs.tiles, ctx->pval[pbuf], ctx->pval[pbuf ^ 1], ctx->pdk[pbuf], ctx->dkey,
                         s);
     }
-    // many more tiles than fit on the GPU at once: the blends pull tiles from a queue,
-    // longest lists first
-    ctx->queue_on = blend && vs.tiles > kQueueMinTiles;
-    if (ctx->queue_on) launch_queue_order(ctx->ranges, (int)vs.tiles, ctx->queue, s);
-    BlendArgs ba{ctx->ranges, ctx->pval[pbuf], ctx->rec, ctx->views, nv, (int)vs.tiles, ctx->opt.z_near,
-                 ctx->opt.filter, ctx->opt.batch};
-    ba.tile_stride = tile_stride(vs.tiles);
-    ba.queue = ctx->queue_on ? ctx->queue : nullptr;
-    ba.check = &ctx->ctrl->check_bits;
+    // many more tiles than fit on the GPU at once: the blends take the longest lists first
+    ctx->order_on = blend && vs.tiles > kOrderMinTiles;
+    if (ctx->order_on) launch_length_order(ctx->ranges, (int)vs.tiles, ctx->order, s);
+    BlendArgs ba = blend_args(ctx, vs, pbuf);
     if (ro) {
       ba.res_x = ro->x;
       ba.res_part = ro->part;
@@ -439,7 +434,10 @@ int render_views(gs2d_ctx* ctx, const ViewSet& vs, hipStream_t s, bool allow_syn
     }
     if (blend) {
       for (int k = 0; k < nv; ++k)
-        if (vs.v[k].contrib) launch_fill_f32(vs.v[k].contrib, 0.f, vs.v[k].n, s);
+        if (vs.v[k].contrib) {
+          launch_fill_f32(vs.v[k].contrib, 0.f, vs.v[k].n, s);
+          ba.contrib = true;
+        }
       ProfScope ps(ctx, kBlendFwd, s);
       launch_blend_fwd(ba, tw, th, ctx->t_final, ctx->last, work_ptr(ctx, s), s);
     }
@@ -482,8 +480,7 @@ int backward_views(gs2d_ctx* ctx, const gs2d_view_grad* grads, int nv, int acc, 
     GS2D_TRY(ensure_gacc(ctx, vs.items));
   }
   launch_upload_views(vs, ctx->views, s);
-  const BlendArgs ba = blend_args(ctx);
-  if (ba.queue) launch_fill_u32(ba.queue + kQueueHeadBwd, 0u, 1, s);
+  const BlendArgs ba = blend_args(ctx, vs, ctx->pair_buf);
   if (!full) {
     {
       ProfScope ps(ctx, kBlendBwd, s);
@@ -651,7 +648,7 @@ int track_iteration(gs2d_ctx* ctx, const ViewSet& vs, const gs2d_track_args* a, 
   GS2D_TRY(render_views(ctx, vs, s, false, false, nullptr, false, !walk_orders, true));
   const int stride = loss_blocks(vs.max_hw);
   if (vs.items > 0) {
-    BlendArgs ba = blend_args(ctx);
+    BlendArgs ba = blend_args(ctx, vs, ctx->pair_buf);
     ba.loss_part = ctx->part;
     ba.lambda_d = a->lambda_d;
     ba.use_masks = a->use_masks;
@@ -912,7 +909,7 @@ GS2D_API int gs2d_destroy(gs2d_ctx* ctx) {
                   ctx->gacc,      ctx->pkey[0],    ctx->pkey[1],   ctx->pval[0],   ctx->pval[1],   ctx->pkey_keep,
                   ctx->pval_keep, ctx->ranges,     ctx->t_final,   ctx->last,      ctx->lgrad,     ctx->limg,
                   ctx->part,      ctx->lpart,      ctx->pose0,     ctx->saved_pose, ctx->views,    ctx->ctrl,
-                  ctx->queue,     ctx->pdk[0],     ctx->pdk[1]};
+                  ctx->order,     ctx->pdk[0],     ctx->pdk[1]};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   if (ctx->host_ctrl) (void)hipHostFree(ctx->host_ctrl);

@@ -3,8 +3,11 @@
 // Forward (Sec. "2D Gaussian Splatting", eq:alpha_blending): one workgroup per
 // screen tile, one lane per pixel, each wave owning an 8x8 block of the tile.
 // The tile's depth-ordered surfel list is staged through LDS in batches of
-// records; every wave tests each record's footprint box against its own
-// 8x8 block (a scalar, wave-uniform branch) before any lane evaluates it.  Per
+// records; every wave keeps those whose footprint may touch its own 8x8 block,
+// tests them against each of its 64 pixels in windows of 32 (a quadratic form,
+// window_hits), and every lane then walks its own pixel's candidates: lanes read
+// different entries, but nearly every lane of a step has one that covers its pixel
+// (a wave that walked one entry at a time had a third of them).  Per
 // (pixel, surfel) pair the ray-splat intersection is solved in the surfel's uv
 // frame from the centre-relative homography rows (see gs2d_internal.h), the
 // Gaussian G = exp(-(u^2+v^2)/2) (or the low-pass filter term) gives
@@ -23,13 +26,22 @@
 // has (u, v) = (0, 0).  Hence the pose gradient of eq:derivatives is, pair by
 // pair, rho += V and phi += X x V (+ n x g_n) with X = mu_c + u a + v b the
 // intersection point.  Pose-only mode accumulates those six numbers in
-// registers and reduces them once per workgroup (no per-surfel atomics); the
-// full mode reduces the 16 per-surfel terms over each wave and adds them
-// atomically.
-#include <mutex>
-#include <vector>
-
+// registers, walking per lane as the forward does, and reduces them once per
+// workgroup (no per-surfel atomics); the full mode walks per 4x4 pixel block (16
+// lanes on one entry, four entries in a wave), reduces the 16 per-surfel terms over
+// each group and adds them atomically.
+//
+// All of it is bound by VALU issue and the latency of the serial steps.  Measured
+// against one entry per wave and step, 640 x 480 views of a 300k-surfel room with 80k
+// to 285k pairs: forward 33 -> 25 to 143 -> 86 us, with contributions 35 -> 27 to
+// 164 -> 80 us; full backward of five views 215 -> 187 to 274 -> 249 us; pose-only
+// backward of a 427 x 239 view 20 -> 17 to 72 -> 48 us; tracking walk 48 -> 35 to
+// 214 -> 121 us.
 #include "tile_order.h"
+
+// The lane-write intrinsic, which has no builtin: `old` with lane `lane` replaced by the
+// wave-uniform `value`.
+extern "C" __device__ int gs2d_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 
 namespace gs2d {
 namespace {
@@ -42,7 +54,9 @@ struct Hit {
 // One (pixel, surfel) evaluation; the forward and backward kernels call this same
 // function so that every decision is reproduced bit for bit.  Returns 0 outside
 // the footprint (rho > 9 or depth < z_near), 1 inside it but below the opacity
-// threshold, 2 when the pair is composited.
+// threshold, 2 when the pair is composited.  No early exit: a wave's lanes evaluate
+// pairs that the window test passed, nearly all of them inside the footprint, and the
+// branches' lane-mask bookkeeping cost more than the exponential they skipped.
 __device__ __forceinline__ int evaluate(float px, float py, float ox, float oy, const float4 g1, const float4 g2,
                                         const float4 g3, float o, float z_near, int filter, Hit& h) {
   // (ox, oy): the integer box corner; g1.xy: the projected centre relative to it
@@ -63,12 +77,12 @@ __device__ __forceinline__ int evaluate(float px, float py, float ox, float oy, 
   h.b3d = rho3 <= rho2;  // NaN (q2 = 0) selects the filter branch
   const float rho = h.b3d ? rho3 : rho2;
   h.d = h.b3d ? fmaf(m0, h.u, fmaf(m1, h.v, m2)) : m2;
-  if (!(rho <= kRhoCutoff) || !(h.d >= z_near)) return 0;
   h.G = __builtin_amdgcn_exp2f(rho * -0.72134752044448170368f);  // exp(-rho / 2)
   const float og = o * h.G;
   h.clamped = og > kAlphaMax;
   h.alpha = h.clamped ? kAlphaMax : og;
-  return h.alpha >= kAlphaMin ? 2 : 1;
+  const bool in = (rho <= kRhoCutoff) & (h.d >= z_near);
+  return in ? (h.alpha >= kAlphaMin ? 2 : 1) : 0;
 }
 
 __device__ __forceinline__ void add_work(unsigned long long* work, int lane, int a, int b) {
@@ -83,15 +97,15 @@ __device__ __forceinline__ void add_work(unsigned long long* work, int lane, int
   }
 }
 
+// The value every lane holds, in a scalar register.
 __device__ __forceinline__ float uniformf(float x) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 
-// Issue priority of a wave by the length of the list it walks: all tiles' workgroups
+// Issue priority of a wave by the length of the list it walks: many tiles' workgroups
 // are resident at once, and a long list is the critical path of the launch, so its
 // waves take the SIMD before the short ones (which fill the remaining slots).
 __device__ __forceinline__ void prioritise(int len) {
-  __builtin_amdgcn_s_setprio(0);  // a persistent workgroup's next tile starts from 0
   if (len >= 192)
     __builtin_amdgcn_s_setprio(3);
   else if (len >= 128)
@@ -100,21 +114,23 @@ __device__ __forceinline__ void prioritise(int len) {
     __builtin_amdgcn_s_setprio(1);
 }
 
-// The tile of a workgroup of a direct (one workgroup per tile) launch: workgroups are
-// dealt round-robin to the 8 XCDs, so each XCD gets every 8th tile of the stride:
-// an even share of the dense and sparse image regions.
+// The tile of a workgroup.  With an order (many more tiles than fit on the GPU at once):
+// the order's, longest lists first, so that the long lists start first and the short ones
+// fill in at the end.  Otherwise workgroups are dealt round-robin to the 8 XCDs, so each
+// XCD gets every 8th tile of the stride: an even share of the dense and sparse image
+// regions.
 __device__ __forceinline__ int grid_tile(const BlendArgs& a) {
+  if (a.order) return __builtin_amdgcn_readfirstlane((int)a.order[blockIdx.x]);
   return (int)(((uint64_t)blockIdx.x * (uint64_t)a.tile_stride) % (uint64_t)a.n_tiles);
 }
 
-// The next item of a persistent launch's queue for the whole workgroup (every thread
-// calls it; the previous item's LDS is free once everyone has passed the first barrier).
-__device__ __forceinline__ int next_queue_item(uint32_t* head) {
-  __shared__ int s_item;
-  __syncthreads();
-  if (threadIdx.x == 0) s_item = (int)atomicAdd(head, 1u);
-  __syncthreads();
-  return s_item;
+// The view of a global tile: lane k compares with view k's first tile, one load for the
+// search (a binary search is up to five dependent ones at the start of every tile).
+__device__ __forceinline__ const ViewDesc& tile_view(const BlendArgs& a, int tile) {
+  if (a.n_views == 1) return a.views[0];
+  const int k = min((int)(threadIdx.x & 63u), a.n_views - 1);
+  const uint64_t m = __ballot(a.views[k].tile_base <= tile) & (~0ull >> (64 - a.n_views));
+  return a.views[__builtin_popcountll(m) - 1];
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -128,24 +144,32 @@ __device__ __forceinline__ int wave_max(int v) {
   return v;
 }
 
-// Per staged entry, what the waves' cull reads: the footprint box, the 3-sigma
-// ellipse (centre relative to the box corner, support matrix Sxx, Sxy) and
-// (Syy, low-pass disc centre relative to the box corner, free word; the backward
-// keeps the entry's surfel id there).
-constexpr int kLdsRec = 6;  // record float4 kept per staged entry ([6] feeds the cull only)
-
-struct CullLds {
-  float4* box;
-  float4* ell;
-  float4* ell2;
-};
-__device__ __forceinline__ void stage_cull(const CullLds& c, int j, int f, const float4& v) {
-  if (f == 0) c.box[j] = v;
-  if (f == 6) c.ell[j] = v;
-  if (f == 5) c.ell2[j].x = v.w;
-  if (f == 1) {
-    c.ell2[j].y = v.x;
-    c.ell2[j].z = v.y;
+// Stages the records of n entries (ids id_of(0 .. n)) in LDS as they are in memory, 7
+// float4 each.  The 28-word stride spreads lanes that read different entries over every
+// bank.  Each thread issues four independent id and record loads before its first store:
+// a batch then costs one round trip to memory instead of one per loop trip (indices past
+// the end repeat the last float4).  store_id(j, id) sees each entry's id once or more.
+constexpr int kStageLoads = 4;
+template <int NT, typename IdOf, typename StoreId>
+__device__ __forceinline__ void stage_records(float4* srec, const float4* __restrict__ rec, int n, int t, IdOf id_of,
+                                              StoreId store_id) {
+  const int last = n * kRecF4 - 1;
+  for (int k0 = t; k0 <= last; k0 += kStageLoads * NT) {
+    int k[kStageLoads];
+    uint32_t id[kStageLoads];
+    float4 v[kStageLoads];
+#pragma unroll
+    for (int u = 0; u < kStageLoads; ++u) {
+      k[u] = min(k0 + u * NT, last);
+      id[u] = id_of(k[u] / kRecF4);
+    }
+#pragma unroll
+    for (int u = 0; u < kStageLoads; ++u) v[u] = rec[(size_t)id[u] * kRecF4 + k[u] % kRecF4];
+#pragma unroll
+    for (int u = 0; u < kStageLoads; ++u) {
+      srec[k[u]] = v[u];
+      if (k[u] % kRecF4 == 0) store_id(k[u] / kRecF4, id[u]);
+    }
   }
 }
 
@@ -159,15 +183,17 @@ __device__ __forceinline__ void stage_cull(const CullLds& c, int j, int f, const
 // direction from its centre to the block's centre, the disc by its distance.  Half
 // a pixel of slack keeps the test conservative against the per-pixel FP32
 // evaluation, so dropping changes no image.
-__device__ __forceinline__ uint64_t overlap_mask(const CullLds& c, int c0, int nb, int lane, float bx0, float by0,
+__device__ __forceinline__ uint64_t overlap_mask(const float4* srec, int c0, int nb, int lane, float bx0, float by0,
                                                  int filter, int pos0, int limit) {
   const int j = c0 + lane;
   bool hit = false;
   if (j < nb && pos0 + j < limit) {
-    const float4 bb = c.box[j];
+    const float4* const r = srec + j * kRecF4;
+    const float4 bb = r[0];
     hit = !(bb.y < bx0 || bb.x > bx0 + 7.0f || bb.w < by0 || bb.z > by0 + 7.0f);
     if (hit) {
-      const float4 e = c.ell[j], e2 = c.ell2[j];
+      const float4 e = r[6];
+      const float syy = r[5].w, cxr = r[1].x, cyr = r[1].y;
       // block corner relative to the box corner (integers: exact)
       const float rx = bx0 - bb.x, ry = by0 - bb.z;
       float nx = rx + 3.5f - e.x, ny = ry + 3.5f - e.y;
@@ -177,16 +203,16 @@ __device__ __forceinline__ uint64_t overlap_mask(const CullLds& c, int c0, int n
         const float inv = __builtin_amdgcn_rsqf(n2);
         nx *= inv;
         ny *= inv;
-        const float ext = __builtin_amdgcn_sqrtf(fmaxf(nx * nx * e.z + 2.0f * nx * ny * e.w + ny * ny * e2.x, 0.0f));
+        const float ext = __builtin_amdgcn_sqrtf(fmaxf(nx * nx * e.z + 2.0f * nx * ny * e.w + ny * ny * syy, 0.0f));
         const float box_lo = nx * (rx + 3.5f) + ny * (ry + 3.5f) - 3.5f * (fabsf(nx) + fabsf(ny));
         sep_e = box_lo > nx * e.x + ny * e.y + ext + 0.5f;
       }
       bool sep_d = true;
       if (filter) {
-        const float qx = fminf(fmaxf(e2.y, rx), rx + 7.0f), qy = fminf(fmaxf(e2.z, ry), ry + 7.0f);
-        const float dx = e2.y - qx, dy = e2.z - qy;
-        const float r = 2.12132034f + 0.5f;  // sqrt(9 / 2) + slack
-        sep_d = dx * dx + dy * dy > r * r;
+        const float qx = fminf(fmaxf(cxr, rx), rx + 7.0f), qy = fminf(fmaxf(cyr, ry), ry + 7.0f);
+        const float dx = cxr - qx, dy = cyr - qy;
+        const float rd = 2.12132034f + 0.5f;  // sqrt(9 / 2) + slack
+        sep_d = dx * dx + dy * dy > rd * rd;
       }
       hit = !(sep_e && sep_d);
     }
@@ -194,21 +220,131 @@ __device__ __forceinline__ uint64_t overlap_mask(const CullLds& c, int c0, int n
   return __ballot(hit);
 }
 
+// The batch's entries that may touch the wave's block, in list order: list[0 .. n)
+// (one byte each; the wave's own LDS) and their count n.  Entries as overlap_mask.
+// mine (nullable): how many of them lie below the lane's own batch position my_end.
+constexpr int kMaxBatch = 256;
+__device__ __forceinline__ int wave_candidates(const float4* srec, int nb, int lane, float bx0, float by0, int filter,
+                                               int pos0, int limit, uint8_t* list, int my_end = 0,
+                                               int* mine = nullptr) {
+  int n = 0, below = 0;
+  for (int c0 = 0; c0 < nb; c0 += 64) {
+    const uint64_t m = overlap_mask(srec, c0, nb, lane, bx0, by0, filter, pos0, limit);
+    const int rank = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+    if ((m >> lane) & 1ull) list[rank] = (uint8_t)(c0 + lane);
+    n += __builtin_popcountll(m);
+    if (mine) {
+      const int e = my_end - c0;
+      below += __builtin_popcountll(e >= 64 ? m : e > 0 ? m & ((1ull << e) - 1ull) : 0ull);
+    }
+  }
+  if (mine) *mine = below;
+  __builtin_amdgcn_wave_barrier();
+  return n;
+}
+
+// Window test: which of the candidates list[w0 .. w0 + wn), wn <= 32, may cover each of
+// the wave's 64 pixels (bit k of a lane's mask: candidate w0 + k).  Lanes k and k + 32
+// hold candidate k and test it against the 32 pixels of the block's upper and lower half
+// in turn; the comparison's lane mask is then two pixels' masks over the candidates,
+// written to those pixels' lanes.
+//
+// The test is a superset of evaluate's footprint.  With e0, e1 and q = 3 q2 / m2 linear in
+// the pixel, u^2 + v^2 <= 9 is S = e0^2 + e1^2 - q^2 <= 0, a quadratic polynomial in the
+// pixel's place (i, j) within the half block: two multiply-adds per pixel from the
+// coefficients at its corner; the low-pass disc is a third.  evaluate's own rounding and
+// the polynomial's are bounded by a few units of 2^-24 of M0^2 + M1^2 + Mq^2, the M the
+// sums of the terms' magnitudes over the half block: 4e-6 of it is allowed for (66 units),
+// 1e-4 relative in the reciprocal, 1e-3 square pixels for the disc.  A pair it drops has
+// evaluate return 0, so images and gradients stay bitwise the same.
+//
+// 7 VALU instructions per two pixels against the 39 of evaluate per pixel, no LDS reads
+// in the loop, and rows of pixels that are all done (alive: lanes still walking) skipped.
+// QUADS: the lanes' pixel map of the full backward.
+constexpr int kWindow = 32;
+template <bool QUADS = false>
+__device__ __forceinline__ uint32_t window_hits(const float4* srec, const uint8_t* list, int w0, int wn, int lane,
+                                                float bx0, float by0, float rho2_max, uint64_t alive) {
+  const int k = lane & 31;
+  const float4* const rec = srec + (int)list[w0 + min(k, wn - 1)] * kRecF4;
+  const float4 r0 = rec[0], r1 = rec[1], r2 = rec[2], r3 = rec[3];
+  const float s = 3.0003f * __builtin_amdgcn_rcpf(r3.w);
+  const float Q1 = r3.x, P0 = r2.y, P1 = r2.z, Q0 = r2.w, Dt = r1.z * s, k0 = r1.w * s, k1 = r2.x * s;
+  const float dx = (bx0 - r0.x) - r1.x, dy = (by0 + (float)((lane >> 5) * 4) - r0.z) - r1.y;
+  const float e0 = fmaf(Q1, dx, -(P1 * dy)), e1 = fmaf(P0, dy, -(Q0 * dx)), q = fmaf(-dy, k1, fmaf(-dx, k0, Dt));
+  const float X = fabsf(dx) + 7.0f, Y = fabsf(dy) + 3.0f;
+  const float M0 = fmaf(fabsf(Q1), X, fabsf(P1) * Y), M1 = fmaf(fabsf(P0), Y, fabsf(Q0) * X);
+  const float Mq = fmaf(fabsf(k0), X, fmaf(fabsf(k1), Y, fabsf(Dt)));
+  const float eps = fmaf(4e-6f, fmaf(M0, M0, fmaf(M1, M1, Mq * Mq)), 1e-30f);
+  // S(i, j) = (A i + B j + D) i + (C j + E) j + F
+  const float A = fmaf(Q1, Q1, fmaf(Q0, Q0, -(k0 * k0))), C = fmaf(P1, P1, fmaf(P0, P0, -(k1 * k1)));
+  const float B = -2.0f * fmaf(Q1, P1, fmaf(P0, Q0, k0 * k1));
+  const float D = 2.0f * fmaf(e0, Q1, fmaf(-e1, Q0, q * k0)), E = 2.0f * fmaf(-e0, P1, fmaf(e1, P0, q * k1));
+  const bool in_window = k < wn;
+  const float F = in_window ? fmaf(e0, e0, fmaf(e1, e1, -(q * q))) - eps : __builtin_inff();
+  // (coefficients that could overflow: every pixel passes)
+  const float r2m = in_window ? (eps < 1e30f ? rho2_max : __builtin_inff()) : -__builtin_inff();
+  int mask = 0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (((alive >> (QUADS ? 16 * r : 8 * r)) & (QUADS ? 0xffffull : 0x000000ff000000ffull)) == 0ull) continue;
+    const float Br = fmaf(B, (float)r, D), Cr = fmaf(fmaf(C, (float)r, E), (float)r, F);
+    const float y = dy + (float)r, Rr = fmaf(y, y, -r2m);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float S = fmaf(fmaf(A, (float)i, Br), (float)i, Cr);
+      const float x = dx + (float)i;
+      const uint64_t m = __ballot(fminf(S, fmaf(x, x, Rr)) <= 0.f);
+      // the lanes of the wave's pixels (i, r) and (i, r + 4)
+      const int l0 = QUADS ? 16 * r + i : 8 * r + i;
+      mask = gs2d_writelane((int)(uint32_t)m, l0, mask);
+      mask = gs2d_writelane((int)(uint32_t)(m >> 32), l0 + (QUADS ? 8 : 32), mask);
+    }
+  }
+  return (uint32_t)mask;
+}
+// The batch position of a lane's next candidate (of any, when m is 0), read ahead of
+// its use.
+__device__ __forceinline__ int next_entry(const uint8_t* list, int w0, uint32_t m) {
+  return list[w0 + __builtin_ctz(m | 0x80000000u)];
+}
+__device__ __forceinline__ int last_entry(const uint8_t* list, int w0, uint32_t m) {
+  return list[w0 + 31 - __builtin_clz(m | 1u)];
+}
+// Windows of up to this many candidates skip the test: every lane evaluates all of them
+// (the test costs the same 300 instructions, seven evaluations, for any window; lines at
+// 4, 8 and 12 measure the same, a tracking iteration of the eight mixed rooms 404 us).
+constexpr int kMinWindow = 8;
+__device__ __forceinline__ float window_rho2(int filter) { return filter ? kRhoCutoff / kFilterScale + 1e-3f : -1.0f; }
+// Each lane's mask over a window's candidates (alive: as window_hits).
+template <bool QUADS = false>
+__device__ __forceinline__ uint32_t window_mask(const float4* srec, const uint8_t* list, int w0, int wn, int lane,
+                                                float bx0, float by0, float rho2_max, uint64_t alive) {
+  if (wn <= kMinWindow) return (1u << wn) - 1u;
+  return window_hits<QUADS>(srec, list, w0, wn, lane, bx0, by0, rho2_max, alive);
+}
+
 // A staged record: box corner (x0, y0), rows g1..g3, (o, rgb), normal.
 struct Rec {
   float ox, oy;
   float4 g1, g2, g3, c4, nv;
 };
+// All of it at once (volatile: a load moved down to its use would add an LDS round trip
+// to each step of a lane's serial walk).
+template <bool NORMAL = true>
 __device__ __forceinline__ Rec load_rec(const float4* srec, int j) {
+  typedef float v4f __attribute__((ext_vector_type(4)));
+  using lv4f = const volatile __attribute__((address_space(3))) v4f;
+  lv4f* const p = (lv4f*)(srec + j * kRecF4);
+  const v4f a = p[0], g1 = p[1], g2 = p[2], g3 = p[3], c4 = p[4], nv = NORMAL ? p[5] : c4;
   Rec r;
-  const float4 bb = srec[j * kLdsRec];
-  r.ox = bb.x;
-  r.oy = bb.z;
-  r.g1 = srec[j * kLdsRec + 1];
-  r.g2 = srec[j * kLdsRec + 2];
-  r.g3 = srec[j * kLdsRec + 3];
-  r.c4 = srec[j * kLdsRec + 4];
-  r.nv = srec[j * kLdsRec + 5];
+  r.ox = a.x;
+  r.oy = a.z;
+  r.g1 = make_float4(g1.x, g1.y, g1.z, g1.w);
+  r.g2 = make_float4(g2.x, g2.y, g2.z, g2.w);
+  r.g3 = make_float4(g3.x, g3.y, g3.z, g3.w);
+  r.c4 = make_float4(c4.x, c4.y, c4.z, c4.w);
+  r.nv = make_float4(nv.x, nv.y, nv.z, nv.w);
   return r;
 }
 
@@ -222,54 +358,25 @@ struct FwdPix {
 // Front-to-back compositing of one evaluated entry (list position pos); returns the
 // entry's blending weight at this pixel (0 when it is not composited).
 __device__ __forceinline__ float composite(FwdPix& s, int code, const Hit& h, const Rec& r, int pos) {
-  if (s.done || code != 2) return 0.f;
   const float Tn = s.T * (1.0f - h.alpha);
-  if (Tn < kTMin) {
-    s.done = true;
-    return 0.f;
+  const bool stop = (code == 2) & (Tn < kTMin);
+  s.done |= stop;
+  float w = 0.f;
+  if ((code == 2) & !stop) {
+    w = h.alpha * s.T;
+    s.cr = fmaf(w, r.c4.y, s.cr);
+    s.cg = fmaf(w, r.c4.z, s.cg);
+    s.cb = fmaf(w, r.c4.w, s.cb);
+    s.cd = fmaf(w, h.d, s.cd);
+    s.n0 = fmaf(w, r.nv.x, s.n0);
+    s.n1 = fmaf(w, r.nv.y, s.n1);
+    s.n2 = fmaf(w, r.nv.z, s.n2);
+    s.co += w;
+    s.dmed = s.T > 0.5f ? h.d : s.dmed;
+    s.T = Tn;
+    s.lastj = pos + 1;
   }
-  const float w = h.alpha * s.T;
-  s.cr = fmaf(w, r.c4.y, s.cr);
-  s.cg = fmaf(w, r.c4.z, s.cg);
-  s.cb = fmaf(w, r.c4.w, s.cb);
-  s.cd = fmaf(w, h.d, s.cd);
-  s.n0 = fmaf(w, r.nv.x, s.n0);
-  s.n1 = fmaf(w, r.nv.y, s.n1);
-  s.n2 = fmaf(w, r.nv.z, s.n2);
-  s.co += w;
-  if (s.T > 0.5f) s.dmed = h.d;
-  s.T = Tn;
-  s.lastj = pos + 1;
   return w;
-}
-
-// Sum over the wave, left in lane 63 (other lanes hold partial sums): an inclusive scan
-// inside each 16-lane row by DPP row shifts, then the row totals carried forward by the
-// row broadcasts of lanes 15 and 31.  Every lane of the wave must be active.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_add(float x) {
-  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, 0xf, false));
-}
-__device__ __forceinline__ float wave_total_lane63(float x) {
-  x = dpp_add<0x111, 0xf>(x);  // row_shr:1
-  x = dpp_add<0x112, 0xf>(x);  // row_shr:2
-  x = dpp_add<0x114, 0xf>(x);  // row_shr:4
-  x = dpp_add<0x118, 0xf>(x);  // row_shr:8
-  x = dpp_add<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
-  x = dpp_add<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
-  return x;
-}
-
-// eq:contribution: the wave's weights of one entry, added to the surfel's sum (one
-// atomic per wave and entry, none where the wave has no weight for it).  Every lane of
-// the wave calls it.
-__device__ __forceinline__ void add_contribution(float* contrib, uint32_t surfel, float w, int lane) {
-  if (__ballot(w != 0.f) == 0ull) return;
-  const float ws = wave_total_lane63(w);
-  // a global (not flat) atomic: flat ones also hold the LDS counter the walk waits on
-  using gfloat = __attribute__((address_space(1))) float;
-  if (lane == 63)
-    __hip_atomic_fetch_add((gfloat*)(contrib + surfel), ws, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 template <int TW, int TH, bool PROF>
@@ -278,10 +385,15 @@ __device__ __forceinline__ void blend_fwd_tile(const BlendArgs& a, const int til
                                                unsigned long long* __restrict__ work) {
   constexpr int NT = TW * TH, WX = TW / 8;
   extern __shared__ float4 srec[];
-  const CullLds cull{srec + (size_t)a.batch * kLdsRec, srec + (size_t)a.batch * (kLdsRec + 1),
-                     srec + (size_t)a.batch * (kLdsRec + 2)};
-  uint32_t* const sids = reinterpret_cast<uint32_t*>(srec + (size_t)a.batch * (kLdsRec + 3));
-  const ViewDesc& V = a.views[view_of_tile(a.views, a.n_views, tile)];
+  // launches with a contribution output: per staged entry the block's sum of its blending
+  // weights (zero between batches) and the surfel id.  The sums are in units of 2^-40
+  // (weights are below 1, a tile has at most 512 pixels): the LDS adds 64-bit integers at
+  // 7 cycles per wave without conflicts and 2 per lane with, floats at 4 per lane always
+  using lu64 = __attribute__((address_space(3))) unsigned long long;
+  unsigned long long* const scon = reinterpret_cast<unsigned long long*>(srec + (size_t)a.batch * kRecF4);
+  uint32_t* const sids = reinterpret_cast<uint32_t*>(scon + a.batch);
+  __shared__ uint8_t s_list[NT / 64][kMaxBatch];
+  const ViewDesc& V = tile_view(a, tile);
   const int lt = tile - V.tile_base;
   const int tx = lt % V.tiles_x, ty = lt / V.tiles_x;
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
@@ -298,55 +410,60 @@ __device__ __forceinline__ void blend_fwd_tile(const BlendArgs& a, const int til
   // read once: the contribution atomics could alias the view table for the compiler
   float* const contrib = V.contrib;
   const uint32_t item_base = (uint32_t)V.item_base;
+  uint8_t* const list = s_list[wave];
+  const float rho2_max = window_rho2(a.filter);
   int n_eval = 0, n_cov = 0;
+  if (contrib)  // the view, and so this branch, is uniform over the workgroup
+    for (int k = t; k < a.batch; k += NT) scon[k] = 0ull;
   for (int b0 = start; b0 < end; b0 += a.batch) {
     if (__syncthreads_count(!s.done) == 0) break;
     const int nb = min(a.batch, end - b0);
-    for (int k = t; k < nb * kRecF4; k += NT) {
-      const int j = k / kRecF4, f = k - j * kRecF4;
-      const uint32_t id = a.pval[b0 + j];
-      const float4 v = a.rec[(size_t)id * kRecF4 + f];
-      if (f < kLdsRec) srec[j * kLdsRec + f] = v;
-      if (f == 0) sids[j] = id;
-      stage_cull(cull, j, f, v);
-    }
+    stage_records<NT>(srec, a.rec, nb, t, [&](int j) { return a.pval[b0 + j]; },
+                      [&](int j, uint32_t id) {
+                        if (contrib) sids[j] = id;
+                      });
     __syncthreads();
     const int pos0 = b0 - start;
-    for (int c0 = 0; c0 < nb; c0 += 64) {
-      if (__ballot(!s.done) == 0ull) break;
-      uint64_t m = overlap_mask(cull, c0, nb, lane, bx0, by0, a.filter, 0, nb);
-      // two overlapping entries per step: their evaluations are independent, the
-      // compositing stays in list order
-      while (m != 0ull) {
-        const int j1 = c0 + __builtin_ctzll(m);
-        m &= m - 1ull;
-        const bool two = m != 0ull;
-        const int j2 = two ? c0 + __builtin_ctzll(m) : j1;
-        if (two) m &= m - 1ull;
-        float w1 = 0.f, w2 = 0.f;
-        if (!s.done) {
-          const Rec r1 = load_rec(srec, j1), r2 = load_rec(srec, j2);
-          Hit h1, h2;
-          const int k1 = evaluate(fpx, fpy, r1.ox, r1.oy, r1.g1, r1.g2, r1.g3, r1.c4.x, a.z_near, a.filter, h1);
-          const int k2 = evaluate(fpx, fpy, r2.ox, r2.oy, r2.g1, r2.g2, r2.g3, r2.c4.x, a.z_near, a.filter, h2);
-          if (PROF) {
-            n_eval += 1;
-            n_cov += k1 > 0;
-          }
-          w1 = composite(s, k1, h1, r1, pos0 + j1);
-          if (two && !s.done) {
-            if (PROF) {
-              n_eval += 1;
-              n_cov += k2 > 0;
-            }
-            w2 = composite(s, k2, h2, r2, pos0 + j2);
-          }
+    const int nc = wave_candidates(srec, nb, lane, bx0, by0, a.filter, 0, nb, list);
+    for (int w0 = 0; w0 < nc; w0 += kWindow) {
+      const uint64_t alive = __ballot(!s.done);
+      if (alive == 0ull) break;
+      const int wn = min(kWindow, nc - w0);
+      uint32_t m = window_mask(srec, list, w0, wn, lane, bx0, by0, rho2_max, alive);
+      // each lane walks its own pixel's candidates, in list order
+      if (s.done) m = 0u;
+      int jn = next_entry(list, w0, m);
+      while (m != 0u) {
+        const int j = jn;
+        const Rec r = load_rec(srec, j);
+        m &= m - 1u;
+        jn = next_entry(list, w0, m);
+        Hit h;
+        const int k = evaluate(fpx, fpy, r.ox, r.oy, r.g1, r.g2, r.g3, r.c4.x, a.z_near, a.filter, h);
+        if (PROF) {
+          n_eval += 1;
+          n_cov += k > 0;
         }
-        if (contrib) {  // the view, and so this branch, is uniform over the workgroup
-          add_contribution(contrib, sids[j1] - item_base, w1, lane);
-          if (two) add_contribution(contrib, sids[j2] - item_base, w2, lane);
+        const float w = composite(s, k, h, r, pos0 + j);
+        m = s.done ? 0u : m;
+        if (contrib && w != 0.f) {
+          const float hi = floorf(w * 256.0f), lo = fmaf(w, 256.0f, -hi) * 4294967296.0f;
+          __hip_atomic_fetch_add((lu64*)(scon + j), ((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo,
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        if (__ballot(!s.done) == 0ull) break;
+      }
+    }
+    if (contrib) {
+      // eq:contribution: one global atomic per entry with any weight in the tile
+      __syncthreads();
+      using gfloat = __attribute__((address_space(1))) float;
+      for (int k = t; k < nb; k += NT) {
+        const unsigned long long ws = scon[k];
+        if (ws != 0ull) {
+          __hip_atomic_fetch_add((gfloat*)(contrib + (sids[k] - item_base)), (float)((double)ws * 0x1p-40),
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          scon[k] = 0ull;
+        }
       }
     }
   }
@@ -397,20 +514,14 @@ __device__ __forceinline__ void blend_fwd_tile(const BlendArgs& a, const int til
   }
 }
 
+// Waves per SIMD: the walk is bound by the latency of its serial steps, and six waves
+// (80 VGPRs, no spill) hide it as well as eight (64, with the window test's coefficients
+// spilled): 120 us against 131 for five 640 x 480 views.  512-thread tiles need eight for
+// a fourth workgroup on the CU (8 views of a 1M-surfel map: 396 us against 414).
 template <int TW, int TH, bool PROF>
-__global__ __launch_bounds__(TW* TH) void blend_fwd_kernel(BlendArgs a, float* __restrict__ t_final,
-                                                           uint32_t* __restrict__ last_out,
-                                                           unsigned long long* __restrict__ work) {
-  if (a.queue) {
-    // persistent: tiles in the queue's order (longest lists first) until it is empty
-    for (;;) {
-      const int item = next_queue_item(a.queue + kQueueHeadFwd);
-      if (item >= a.n_tiles) break;
-      blend_fwd_tile<TW, TH, PROF>(a, (int)a.queue[kQueueOrder + item], t_final, last_out, work);
-    }
-  } else {
-    blend_fwd_tile<TW, TH, PROF>(a, grid_tile(a), t_final, last_out, work);
-  }
+__global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(TW * TH > 256 ? 8 : 6))) void blend_fwd_kernel(
+    BlendArgs a, float* __restrict__ t_final, uint32_t* __restrict__ last_out, unsigned long long* __restrict__ work) {
+  blend_fwd_tile<TW, TH, PROF>(a, grid_tile(a), t_final, last_out, work);
 }
 
 // Per-pixel state of the backward walk.
@@ -421,73 +532,72 @@ struct BwdPix {
   float pr0, pr1, pr2, pp0, pp1, pp2;        // pose gradient (pose-only mode)
 };
 
-// Reverse mode of one composited entry: updates the walk state and either the
-// pose sums (pose-only) or the entry's 16 per-surfel terms acc.
+// What the full mode's 16 per-surfel terms of a pair are made of: V (with u V and v V),
+// the opacity's gradient, and w times the pixel's colour and normal gradients.
+struct PairTerms {
+  float Vx, Vy, Vz, u, v, go, r, g, b, n0, n1, n2;
+};
+
+// Reverse mode of one entry: updates the walk state and either the pose sums (pose-only)
+// or the pair's terms t.  Where the entry is not composited at the pixel (!on) it leaves
+// the state as it is (an opacity of 0) and gives zero terms: nothing the pair computes
+// there, finite or not, reaches a sum.
 template <bool POSE_ONLY, bool HAS_N, bool HAS_O>
-__device__ __forceinline__ void reverse_entry(BwdPix& s, const Hit& h, const Rec& r, const CamF& cam, float xh,
-                                              float yh, float ifx, float ify, float* acc) {
+__device__ __forceinline__ void reverse_entry(BwdPix& s, bool on, const Hit& h, const Rec& r, const CamF& cam, float xh,
+                                              float yh, float ifx, float ify, PairTerms& t) {
   const float4 c4 = r.c4, nv = r.nv;
-  const float al = h.alpha;
+  const float al = on ? h.alpha : 0.f, hd = on ? h.d : 0.f, G = on ? h.G : 0.f;
+  const bool b3d = on & h.b3d;
   const float Tj = s.T * __builtin_amdgcn_rcpf(1.0f - al);
   const float w = al * Tj;
-  float dLda = s.gr * (c4.y - s.Br) + s.gg * (c4.z - s.Bg) + s.gb * (c4.w - s.Bb) + s.gd * (h.d - s.Bd);
-  if (HAS_N) dLda += s.gn0 * (nv.x - s.Bn0) + s.gn1 * (nv.y - s.Bn1) + s.gn2 * (nv.z - s.Bn2);
+  const float er = c4.y - s.Br, eg = c4.z - s.Bg, eb = c4.w - s.Bb, ed = hd - s.Bd;
+  float dLda = s.gr * er + s.gg * eg + s.gb * eb + s.gd * ed;
+  float e0 = 0.f, e1 = 0.f, e2 = 0.f;
+  if (HAS_N) {
+    // normals, alone among the record's values, are not known to be finite
+    e0 = on ? nv.x - s.Bn0 : 0.f;
+    e1 = on ? nv.y - s.Bn1 : 0.f;
+    e2 = on ? nv.z - s.Bn2 : 0.f;
+    dLda += s.gn0 * e0 + s.gn1 * e1 + s.gn2 * e2;
+  }
   if (HAS_O) dLda += s.go * (1.0f - s.Bo);
   dLda *= Tj;
-  s.Br = fmaf(al, c4.y - s.Br, s.Br);
-  s.Bg = fmaf(al, c4.z - s.Bg, s.Bg);
-  s.Bb = fmaf(al, c4.w - s.Bb, s.Bb);
-  s.Bd = fmaf(al, h.d - s.Bd, s.Bd);
+  s.Br = fmaf(al, er, s.Br);
+  s.Bg = fmaf(al, eg, s.Bg);
+  s.Bb = fmaf(al, eb, s.Bb);
+  s.Bd = fmaf(al, ed, s.Bd);
   if (HAS_N) {
-    s.Bn0 = fmaf(al, nv.x - s.Bn0, s.Bn0);
-    s.Bn1 = fmaf(al, nv.y - s.Bn1, s.Bn1);
-    s.Bn2 = fmaf(al, nv.z - s.Bn2, s.Bn2);
+    s.Bn0 = fmaf(al, e0, s.Bn0);
+    s.Bn1 = fmaf(al, e1, s.Bn1);
+    s.Bn2 = fmaf(al, e2, s.Bn2);
   }
   if (HAS_O) s.Bo = fmaf(al, 1.0f - s.Bo, s.Bo);
   s.T = Tj;
-  const float g_d = w * s.gd;
-  float g_o = 0.f, dLdG = 0.f;
-  if (!h.clamped) {
-    g_o = h.G * dLda;
-    dLdG = c4.x * dLda;
-  }
-  const float dLdrho = -0.5f * h.G * dLdG;
+  auto when_on = [&](float g) { return on ? w * g : 0.f; };  // (a pixel's gradient need not be finite)
+  const float g_d = when_on(s.gd);
+  const float du = on & !h.clamped ? dLda : 0.f;
+  const float g_o = G * du;
+  const float dLdrho = -0.5f * G * (c4.x * du);
   const float m0 = r.g3.y, m1 = r.g3.z, m2 = r.g3.w;
-  float Vx, Vy, Vz, ue, ve, Xx, Xy, Xz;
-  if (h.b3d) {
-    // u = q0/q2, v = q1/q2; depth d = m . (u, v, 1)
-    const float gu = fmaf(2.0f * h.u, dLdrho, m0 * g_d);
-    const float gv = fmaf(2.0f * h.v, dLdrho, m1 * g_d);
-    const float gq0 = gu * h.rq, gq1 = gv * h.rq;
-    // h_u = P - dx m, h_v = Q - dy m (third entries -dx m2, -dy m2)
-    const float hu0 = fmaf(-h.dx, m0, r.g2.y), hu1 = fmaf(-h.dx, m1, r.g2.z);
-    const float hv0 = fmaf(-h.dy, m0, r.g2.w), hv1 = fmaf(-h.dy, m1, r.g3.x);
-    const float V0 = hv0 * gq1 - hv1 * gq0;  // (h_v x g_q)_z
-    const float V1 = gq0 * hu1 - gq1 * hu0;  // (g_q x h_u)_z
-    Vx = cam.fx * V0;
-    Vy = cam.fy * V1;
-    Vz = g_d - xh * Vx - yh * Vy;
-    ue = h.u;
-    ve = h.v;
-    Xx = h.d * xh;
-    Xy = h.d * yh;
-    Xz = h.d;
-  } else {
-    // rho = 2 |p - c|^2 with c = (M02, M12) / m2; depth = m2
-    const float gcx = -2.0f * kFilterScale * h.dx * dLdrho;
-    const float gcy = -2.0f * kFilterScale * h.dy * dLdrho;
-    const float im2 = __builtin_amdgcn_rcpf(m2);
-    Vx = cam.fx * gcx * im2;
-    Vy = cam.fy * gcy * im2;
-    const float xc = ((r.ox + r.g1.x) - cam.cx) * ifx, yc = ((r.oy + r.g1.y) - cam.cy) * ify;
-    Vz = g_d - xc * Vx - yc * Vy;
-    ue = 0.f;
-    ve = 0.f;
-    Xx = m2 * xc;
-    Xy = m2 * yc;
-    Xz = m2;
-  }
+  // 3D branch: u = q0/q2, v = q1/q2; depth d = m . (u, v, 1)
+  const float gu = fmaf(2.0f * h.u, dLdrho, m0 * g_d);
+  const float gv = fmaf(2.0f * h.v, dLdrho, m1 * g_d);
+  const float gq0 = gu * h.rq, gq1 = gv * h.rq;
+  // h_u = P - dx m, h_v = Q - dy m (third entries -dx m2, -dy m2)
+  const float hu0 = fmaf(-h.dx, m0, r.g2.y), hu1 = fmaf(-h.dx, m1, r.g2.z);
+  const float hv0 = fmaf(-h.dy, m0, r.g2.w), hv1 = fmaf(-h.dy, m1, r.g3.x);
+  const float V0 = hv0 * gq1 - hv1 * gq0;  // (h_v x g_q)_z
+  const float V1 = gq0 * hu1 - gq1 * hu0;  // (g_q x h_u)_z
+  // filter branch: rho = 2 |p - c|^2 with c = (M02, M12) / m2; depth = m2; its ray is the
+  // centre's
+  const float im2 = b3d ? 1.0f : __builtin_amdgcn_rcpf(m2);
+  const float Vx = cam.fx * (b3d ? V0 : -2.0f * kFilterScale * h.dx * dLdrho) * im2;
+  const float Vy = cam.fy * (b3d ? V1 : -2.0f * kFilterScale * h.dy * dLdrho) * im2;
+  const float xr = b3d ? xh : ((r.ox + r.g1.x) - cam.cx) * ifx;
+  const float yr = b3d ? yh : ((r.oy + r.g1.y) - cam.cy) * ify;
+  const float Vz = g_d - xr * Vx - yr * Vy;
   if (POSE_ONLY) {
+    const float Xx = hd * xr, Xy = hd * yr, Xz = hd;  // h.d = m2 in the filter branch
     s.pr0 += Vx;
     s.pr1 += Vy;
     s.pr2 += Vz;
@@ -495,78 +605,78 @@ __device__ __forceinline__ void reverse_entry(BwdPix& s, const Hit& h, const Rec
     s.pp1 += Xz * Vx - Xx * Vz;
     s.pp2 += Xx * Vy - Xy * Vx;
     if (HAS_N) {
-      const float w0 = w * s.gn0, w1 = w * s.gn1, w2 = w * s.gn2;
-      s.pp0 += nv.y * w2 - nv.z * w1;
-      s.pp1 += nv.z * w0 - nv.x * w2;
-      s.pp2 += nv.x * w1 - nv.y * w0;
+      const float w0 = when_on(s.gn0), w1 = when_on(s.gn1), w2 = when_on(s.gn2);
+      const float nx = on ? nv.x : 0.f, ny = on ? nv.y : 0.f, nz = on ? nv.z : 0.f;
+      s.pp0 += ny * w2 - nz * w1;
+      s.pp1 += nz * w0 - nx * w2;
+      s.pp2 += nx * w1 - ny * w0;
     }
   } else {
-    acc[0] = Vx;
-    acc[1] = Vy;
-    acc[2] = Vz;
-    acc[3] = ue * Vx;
-    acc[4] = ue * Vy;
-    acc[5] = ue * Vz;
-    acc[6] = ve * Vx;
-    acc[7] = ve * Vy;
-    acc[8] = ve * Vz;
-    acc[9] = w * s.gn0;
-    acc[10] = w * s.gn1;
-    acc[11] = w * s.gn2;
-    acc[12] = w * s.gr;
-    acc[13] = w * s.gg;
-    acc[14] = w * s.gb;
-    acc[15] = g_o;
+    t = PairTerms{Vx, Vy, Vz, b3d ? h.u : 0.f, b3d ? h.v : 0.f, g_o, when_on(s.gr), when_on(s.gg), when_on(s.gb),
+                  0.f, 0.f, 0.f};
+    if (HAS_N) {
+      t.n0 = when_on(s.gn0);
+      t.n1 = when_on(s.gn1);
+      t.n2 = when_on(s.gn2);
+    }
   }
 }
 
 // The value of x at the lane that DPP control CTRL selects (all rows and banks on).
 template <int CTRL>
 __device__ __forceinline__ float dpp_get(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
 }
 
-// Full mode: the wave's sums of one entry's 16 terms, added to the surfel's row.  A
-// transposing butterfly halves the values per lane at each exchange, so that lane bits
-// 5, 4, 3, 2 pick the term, then sums the four lanes of each quad.  Every exchange is a
-// VALU lane move: v_permlane32_swap (lanes L, L^32), v_permlane16_swap (rows 0-1 and
-// 2-3), DPP row_ror:8 (L^8 within a row), DPP row_half_mirror (a lane of the other
-// half of its 8-lane group) and quad_perm.  Lanes 4k hold term k and add it into the
-// entry's 16-float slot of the workgroup's LDS accumulator (one 16-lane ds_add, 16
-// banks), which the block adds to the surfel's row in HBM once per batch.  Every lane
-// of the wave must be active.
-__device__ __forceinline__ void flush_entry(const float* acc, bool contrib, float* sacc, int j, int lane) {
-  if (__ballot(contrib) == 0ull) return;
-  float v16[16], v8[8], v4[4], v2[2];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) v16[k] = contrib ? acc[k] : 0.f;
-  // lanes 0-31 keep terms 0-7 and add lane L+32's; lanes 32-63 keep 8-15 and add L-32's
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v16[i]), __float_as_uint(v16[8 + i]), false,
-                                                    false);
-    v8[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  // rows 0 and 2 keep the lower four, rows 1 and 3 the upper four
+// Full mode: the sums of 16 terms over each of the wave's four 16-lane groups (group g:
+// lanes 16 r + 4 g + c; a group's lanes hold the same entry j, groups may differ; group_on:
+// the group has one).  A transposing butterfly halves the values per lane at each
+// exchange: v_permlane32_swap (L^32) and v_permlane16_swap (L^16), which move two
+// registers in one instruction (an exchange within a row takes two selects), then
+// quad_perm; lane bits 5, 4, 1, 0 pick the term.  Each lane adds its term's total into
+// the entry's 16 slots of the workgroup's LDS accumulator, in double: a conflict-free
+// 64-lane ds_add_f64 takes 9 cycles of the LDS, ds_add_f32 (which the LDS does lane by
+// lane) 193.  Every lane of the wave must be active.
+template <bool HAS_N>
+__device__ __forceinline__ void flush_group(const PairTerms& p, bool group_on, double* sacc, int j, int lane) {
+  const bool h2 = (lane & 2) != 0, h1 = (lane & 1) != 0;
+  float v8[8], v4[4], v2[2];
+  // terms k and k + 8
+  auto first = [&](float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  };
+  v8[0] = first(p.Vx, p.v * p.Vz);
+  v8[1] = first(p.Vy, p.n0);
+  v8[2] = first(p.Vz, p.n1);
+  v8[3] = first(p.u * p.Vx, p.n2);
+  v8[4] = first(p.u * p.Vy, p.r);
+  v8[5] = first(p.u * p.Vz, p.g);
+  v8[6] = first(p.v * p.Vx, p.b);
+  v8[7] = first(p.v * p.Vy, p.go);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v8[i]), __float_as_uint(v8[4 + i]), false,
-                                                    false);
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v8[i]), __float_as_uint(v8[4 + i]), false, false);
     v4[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   }
-  const bool h8 = (lane & 8) != 0, h4 = (lane & 4) != 0;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const float mine = h8 ? v4[2 + i] : v4[i], give = h8 ? v4[i] : v4[2 + i];
-    v2[i] = mine + dpp_get<0x128>(give);  // row_ror:8
-  }
-  float v = (h4 ? v2[1] : v2[0]) + dpp_get<0x141>(h4 ? v2[0] : v2[1]);  // row_half_mirror
-  v += dpp_get<0x4E>(v);  // quad_perm [2, 3, 0, 1]
-  v += dpp_get<0xB1>(v);  // quad_perm [1, 0, 3, 2]
-  const int k = ((lane >> 5) & 1) * 8 + ((lane >> 4) & 1) * 4 + ((lane >> 3) & 1) * 2 + ((lane >> 2) & 1);
-  using lfloat = __attribute__((address_space(3))) float;
-  if ((lane & 3) == 0)
-    __hip_atomic_fetch_add((lfloat*)(sacc + j * 16 + k), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  for (int i = 0; i < 2; ++i) v2[i] = (h2 ? v4[2 + i] : v4[i]) + dpp_get<0x4E>(h2 ? v4[i] : v4[2 + i]);
+  const float v = (h1 ? v2[1] : v2[0]) + dpp_get<0xB1>(h1 ? v2[0] : v2[1]);
+  const int k = ((lane >> 5) & 1) * 8 + ((lane >> 4) & 1) * 4 + (lane & 3);
+  using ldouble = __attribute__((address_space(3))) double;
+  if (group_on)
+    __hip_atomic_fetch_add((ldouble*)(sacc + j * 16 + k), (double)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// The OR of x over the lane's 16-lane group.
+__device__ __forceinline__ uint32_t group_or(uint32_t x) {
+  const auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  x = a[0] | a[1];
+  const auto b = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = b[0] | b[1];
+  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, true);  // quad_perm [2, 3, 0, 1]
+  x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, true);  // quad_perm [1, 0, 3, 2]
+  return x;
 }
 
 template <int TW, int TH, bool POSE_ONLY, bool HAS_N, bool HAS_O, bool PROF>
@@ -575,23 +685,25 @@ __device__ __forceinline__ void blend_bwd_tile(const BlendArgs& a, const int til
                                                float* __restrict__ part, unsigned long long* __restrict__ work) {
   constexpr int NT = TW * TH, WX = TW / 8, NW = NT / 64;
   extern __shared__ float4 srec[];
-  const CullLds cull{srec + (size_t)a.batch * kLdsRec, srec + (size_t)a.batch * (kLdsRec + 1),
-                     srec + (size_t)a.batch * (kLdsRec + 2)};
-  // full mode: per staged entry the block's sums of its 16 terms (zero between
-  // batches); the entry's surfel id rides in the unused last word of its cull data,
-  // which keeps a 256-entry batch within a third of the CU's LDS
-  float* sacc = reinterpret_cast<float*>(srec + (size_t)a.batch * (kLdsRec + 3));
+  // full mode: per staged entry its surfel id and the block's sums of its 16 terms (zero
+  // between batches)
+  uint32_t* const sids = reinterpret_cast<uint32_t*>(srec + (size_t)a.batch * kRecF4);
+  double* const sacc = reinterpret_cast<double*>(sids + a.batch);
   __shared__ int s_wmax[NW];
   __shared__ float s_red[NW][6];
-  const ViewDesc& V = a.views[view_of_tile(a.views, a.n_views, tile)];
+  __shared__ uint8_t s_list[NW][kMaxBatch];  // pose-only mode
+  const ViewDesc& V = tile_view(a, tile);
   const CamF cam = V.cam;
   const int lt = tile - V.tile_base;
   const int tx = lt % V.tiles_x, ty = lt / V.tiles_x;
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   if (!POSE_ONLY)
-    for (int k = t; k < a.batch * 16; k += NT) sacc[k] = 0.f;
+    for (int k = t; k < a.batch * 16; k += NT) sacc[k] = 0.0;
   const int wx0 = tx * TW + (wave % WX) * 8, wy0 = ty * TH + (wave / WX) * 8;
-  const int px = wx0 + (lane & 7), py = wy0 + (lane >> 3);
+  // pose-only: lane = pixel, row by row; full: group g = (lane >> 2) & 3 of 16 lanes is
+  // the wave's g-th 4 x 4 block, one of its pixel rows in each 16-lane row of the wave
+  const int px = wx0 + (POSE_ONLY ? lane & 7 : ((lane >> 2) & 1) * 4 + (lane & 3));
+  const int py = wy0 + (POSE_ONLY ? lane >> 3 : ((lane >> 3) & 1) * 4 + (lane >> 4));
   const bool inside = px < cam.width && py < cam.height;
   const float fpx = (float)px, fpy = (float)py;
   const float bx0 = (float)wx0, by0 = (float)wy0;
@@ -617,7 +729,7 @@ __device__ __forceinline__ void blend_bwd_tile(const BlendArgs& a, const int til
     if (HAS_O && V.g_alpha) s.go = V.g_alpha[p];
   }
   const float xh = (fpx - cam.cx) / cam.fx, yh = (fpy - cam.cy) / cam.fy;
-  const float ifx = 1.0f / cam.fx, ify = 1.0f / cam.fy;
+  const float ifx = uniformf(1.0f / cam.fx), ify = uniformf(1.0f / cam.fy);
   int n_eval = 0, n_cov = 0;
   const uint2 rg = a.ranges[tile];
   GS2D_DCHECK(a.check, tile < a.n_tiles && rg.x <= rg.y, kCheckBlendRange);
@@ -630,49 +742,66 @@ __device__ __forceinline__ void blend_bwd_tile(const BlendArgs& a, const int til
 #pragma unroll
   for (int w = 0; w < NW; ++w) blast = max(blast, s_wmax[w]);
   prioritise(blast);
+  uint8_t* const list = s_list[wave];
+  const float rho2_max = window_rho2(a.filter);
 
   for (int bend = blast; bend > 0; bend -= a.batch) {
     const int bstart = max(0, bend - a.batch);
     const int nb = bend - bstart;
     __syncthreads();
-    for (int k = t; k < nb * kRecF4; k += NT) {
-      const int j = k / kRecF4, f = k - j * kRecF4;
-      const uint32_t id = a.pval[start + bstart + j];
-      const float4 v = a.rec[(size_t)id * kRecF4 + f];
-      if (f < kLdsRec) srec[j * kLdsRec + f] = v;
-      stage_cull(cull, j, f, v);
-      if (f == 0) cull.ell2[j].w = __uint_as_float(id);
-    }
+    stage_records<NT>(srec, a.rec, nb, t, [&](int j) { return a.pval[start + bstart + j]; },
+                      [&](int j, uint32_t id) {
+                        if (!POSE_ONLY) sids[j] = id;
+                      });
     __syncthreads();
-    // chunks of 64 from the back; within a chunk the overlapping entries below the
-    // wave's last position, highest first (two per step in the pose-only mode)
-    for (int c1 = nb; c1 > 0; c1 -= 64) {
-      const int c0 = max(0, c1 - 64);
-      uint64_t m = overlap_mask(cull, c0, c1, lane, bx0, by0, a.filter, bstart, wlast);
-      while (m != 0ull) {
-        const int b1 = 63 - __builtin_clzll(m);
-        m &= ~(1ull << b1);
-        // the full mode takes one entry per step: its 16 terms per entry then fit
-        // 70-80 VGPRs (about 110-120 with two), which doubles the waves per SIMD
-        const bool two = POSE_ONLY && m != 0ull;
-        const int b2 = two ? 63 - __builtin_clzll(m) : b1;
-        if (two) m &= ~(1ull << b2);
-        const int j1 = c0 + b1, j2 = c0 + b2;
-        const Rec r1 = load_rec(srec, j1), r2 = load_rec(srec, j2);
-        const bool live1 = bstart + j1 < my_last, live2 = two && bstart + j2 < my_last;
-        Hit h1, h2;
-        const int k1 = evaluate(fpx, fpy, r1.ox, r1.oy, r1.g1, r1.g2, r1.g3, r1.c4.x, a.z_near, a.filter, h1);
-        const int k2 = evaluate(fpx, fpy, r2.ox, r2.oy, r2.g1, r2.g2, r2.g3, r2.c4.x, a.z_near, a.filter, h2);
-        if (PROF) {
-          n_eval += (int)live1 + (int)live2;
-          n_cov += (int)(live1 && k1 > 0) + (int)(live2 && k2 > 0);
+    // windows from the back; each lane's candidates below its last composited entry
+    int mine;
+    const int nc = wave_candidates(srec, nb, lane, bx0, by0, a.filter, bstart, wlast, list, my_last - bstart, &mine);
+    const uint64_t alive = __ballot(mine > 0);
+    for (int w1 = nc; w1 > 0; w1 -= kWindow) {
+      const int w0 = max(0, w1 - kWindow), wn = w1 - w0;
+      uint32_t m = window_mask<!POSE_ONLY>(srec, list, w0, wn, lane, bx0, by0, rho2_max, alive);
+      const int e = mine - w0;
+      m = e >= kWindow ? m : e > 0 ? m & ((1u << e) - 1u) : 0u;
+      if (POSE_ONLY) {
+        // each lane walks its own, highest first
+        int jn = last_entry(list, w0, m);
+        while (m != 0u) {
+          const Rec r = load_rec<HAS_N>(srec, jn);
+          m &= ~(0x80000000u >> __builtin_clz(m));
+          jn = last_entry(list, w0, m);
+          Hit h;
+          const int k = evaluate(fpx, fpy, r.ox, r.oy, r.g1, r.g2, r.g3, r.c4.x, a.z_near, a.filter, h);
+          if (PROF) {
+            n_eval += 1;
+            n_cov += k > 0;
+          }
+          PairTerms unused;
+          reverse_entry<true, HAS_N, HAS_O>(s, k == 2, h, r, cam, xh, yh, ifx, ify, unused);
         }
-        float acc1[16], acc2[16];
-        const bool c1on = live1 && k1 == 2, c2on = live2 && k2 == 2;
-        if (c1on) reverse_entry<POSE_ONLY, HAS_N, HAS_O>(s, h1, r1, cam, xh, yh, ifx, ify, acc1);
-        if (!POSE_ONLY) flush_entry(acc1, c1on, sacc, j1, lane);
-        if (c2on) reverse_entry<POSE_ONLY, HAS_N, HAS_O>(s, h2, r2, cam, xh, yh, ifx, ify, acc2);
-        if (!POSE_ONLY && two) flush_entry(acc2, c2on, sacc, j2, lane);
+      } else {
+        // each 16-lane group (a 4 x 4 pixel block) walks the union of its lanes' candidates,
+        // highest first: 46 steps per wave and 8 x 8 block where the whole wave's union
+        // has 63 (a dense 640 x 480 room)
+        uint32_t u = group_or(m);
+        int jn = last_entry(list, w0, u);
+        while (__ballot(u != 0u) != 0ull) {
+          const int j = jn;
+          const Rec r = load_rec<HAS_N>(srec, j);
+          const uint32_t bit = u != 0u ? 0x80000000u >> __builtin_clz(u | 1u) : 0u;
+          u &= ~bit;
+          jn = last_entry(list, w0, u);
+          const bool mine_b = (m & bit) != 0u;
+          Hit h;
+          const int k = evaluate(fpx, fpy, r.ox, r.oy, r.g1, r.g2, r.g3, r.c4.x, a.z_near, a.filter, h);
+          if (PROF) {
+            n_eval += (int)mine_b;
+            n_cov += (int)(mine_b && k > 0);
+          }
+          PairTerms pt;
+          reverse_entry<false, HAS_N, HAS_O>(s, mine_b & (k == 2), h, r, cam, xh, yh, ifx, ify, pt);
+          flush_group<HAS_N>(pt, bit != 0u, sacc, j, lane);
+        }
       }
     }
     if (!POSE_ONLY) {
@@ -681,12 +810,12 @@ __device__ __forceinline__ void blend_bwd_tile(const BlendArgs& a, const int til
       __syncthreads();
       using gfloat = __attribute__((address_space(1))) float;
       for (int k = t; k < nb * 16; k += NT) {
-        const float v = sacc[k];
+        const float v = (float)sacc[k];
         if (v != 0.f) {
-          const uint32_t id = __float_as_uint(cull.ell2[k >> 4].w);
+          const uint32_t id = sids[k >> 4];
           __hip_atomic_fetch_add((gfloat*)(gacc + (size_t)id * 16 + (k & 15)), v, __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_AGENT);
-          sacc[k] = 0.f;
+          sacc[k] = 0.0;
         }
       }
     }
@@ -709,28 +838,20 @@ __device__ __forceinline__ void blend_bwd_tile(const BlendArgs& a, const int til
   }
 }
 
+// Four waves per SIMD (95 to 108 VGPRs): five spill the variants with normal gradients
+// (5 views of 640 x 480: 276 us against 268), six every variant (312).
 template <int TW, int TH, bool POSE_ONLY, bool HAS_N, bool HAS_O, bool PROF>
-__global__ __launch_bounds__(TW* TH) void blend_bwd_kernel(BlendArgs a, const float* __restrict__ t_final,
-                                                           const uint32_t* __restrict__ last_in,
-                                                           float* __restrict__ gacc, float* __restrict__ part,
-                                                           unsigned long long* __restrict__ work) {
-  if (a.queue) {
-    for (;;) {
-      const int item = next_queue_item(a.queue + kQueueHeadBwd);
-      if (item >= a.n_tiles) break;
-      blend_bwd_tile<TW, TH, POSE_ONLY, HAS_N, HAS_O, PROF>(a, (int)a.queue[kQueueOrder + item], t_final, last_in,
-                                                            gacc, part, work);
-    }
-  } else {
-    blend_bwd_tile<TW, TH, POSE_ONLY, HAS_N, HAS_O, PROF>(a, grid_tile(a), t_final, last_in, gacc, part, work);
-  }
+__global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(4))) void blend_bwd_kernel(
+    BlendArgs a, const float* __restrict__ t_final, const uint32_t* __restrict__ last_in, float* __restrict__ gacc,
+    float* __restrict__ part, unsigned long long* __restrict__ work) {
+  blend_bwd_tile<TW, TH, POSE_ONLY, HAS_N, HAS_O, PROF>(a, grid_tile(a), t_final, last_in, gacc, part, work);
 }
 
-// float4 slots before the ordered list in the tracking walk's LDS: the staged records
-// and their cull data, or the ordering's scratch, whichever is larger (both are used
+// float4 slots before the ordered list in the tracking walk's LDS: the staged records,
+// or the ordering's scratch, whichever is larger (both are used
 // one after the other)
 __host__ __device__ constexpr int track_stage_f4(int batch) {
-  return batch * (kLdsRec + 3) > (kOrderScratchWords + 3) / 4 ? batch * (kLdsRec + 3) : (kOrderScratchWords + 3) / 4;
+  return batch * kRecF4 > (kOrderScratchWords + 3) / 4 ? batch * kRecF4 : (kOrderScratchWords + 3) / 4;
 }
 
 // Tracking: the forward blend, the tracking loss and the pose-only gradient in one
@@ -751,11 +872,10 @@ template <int TW, int TH, bool PROF>
 __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(5))) void blend_track_kernel(BlendArgs a, unsigned long long* __restrict__ work) {
   constexpr int NT = TW * TH, WX = TW / 8, NW = NT / 64;
   extern __shared__ float4 srec[];
-  const CullLds cull{srec + (size_t)a.batch * kLdsRec, srec + (size_t)a.batch * (kLdsRec + 1),
-                     srec + (size_t)a.batch * (kLdsRec + 2)};
+  __shared__ uint8_t s_list[NW][kMaxBatch];
   __shared__ float s_red[NW][8];
   const int tile = (int)(((uint64_t)blockIdx.x * (uint64_t)a.tile_stride) % (uint64_t)a.n_tiles);
-  const ViewDesc& V = a.views[view_of_tile(a.views, a.n_views, tile)];
+  const ViewDesc& V = tile_view(a, tile);
   const CamF cam = V.cam;
   const int lt = tile - V.tile_base;
   const int tx = lt % V.tiles_x, ty = lt / V.tiles_x;
@@ -766,7 +886,7 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(5))) voi
   const float fpx = (float)px, fpy = (float)py;
   const float bx0 = (float)wx0, by0 = (float)wy0;
   const float xh = (fpx - cam.cx) / cam.fx, yh = (fpy - cam.cy) / cam.fy;
-  const float ifx = 1.0f / cam.fx, ify = 1.0f / cam.fy;
+  const float ifx = uniformf(1.0f / cam.fx), ify = uniformf(1.0f / cam.fy);
   const uint2 rg = a.ranges[tile];
   GS2D_DCHECK(a.check, tile < a.n_tiles && rg.x <= rg.y, kCheckBlendRange);
   const int start = (int)rg.x, end = (int)rg.y;
@@ -785,22 +905,22 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(5))) voi
 #pragma unroll
   for (int k = 0; k < 6; ++k) Q[k] = Ar[k] = Ag[k] = Ab[k] = AD[k] = 0.f;
   int n_eval = 0, n_cov = 0;
+  uint8_t* const list = s_list[wave];
+  const float rho2_max = window_rho2(a.filter);
   // one composited entry: the forward blend and the gradient terms
   auto step = [&](int code, const Hit& h, const Rec& r) {
-    if (s.done || code != 2) return;
     const float al = h.alpha;
     const float Tn = s.T * (1.0f - al);
-    if (Tn < kTMin) {
-      s.done = true;
-      return;
-    }
+    const bool stop = (code == 2) & (Tn < kTMin);
+    s.done |= stop;
+    if ((code != 2) | stop) return;
     const float T = s.T, w = al * T;
     const float m0 = r.g3.y, m1 = r.g3.z, m2 = r.g3.w;
     // V = dLdrho V_rho + g_d V_d for the pair (see the backward kernel); J and K are
     // [V; X x V] with X = d (xr, yr, 1) the intersection point: X x V = d (r x V)
     // with r = (xr, yr, 1) the ray through the pixel (or, in the filter branch, through
     // the projected centre).
-    float Vr0, Vr1, Vd0, Vd1, Vd2, d;
+    float Vr0, Vr1, Vd0 = 0.f, Vd1 = 0.f, xr = xh, yr = yh;
     if (h.b3d) {
       const float hu0 = fmaf(-h.dx, m0, r.g2.y), hu1 = fmaf(-h.dx, m1, r.g2.z);
       const float hv0 = fmaf(-h.dy, m0, r.g2.w), hv1 = fmaf(-h.dy, m1, r.g3.x);
@@ -811,25 +931,19 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(5))) voi
       Vr1 = (cam.fy * r2) * fmaf(hu1, h.u, -(hu0 * h.v));
       Vd0 = (cam.fx * h.rq) * fmaf(r.g2.w, m1, -(r.g3.x * m0));
       Vd1 = (cam.fy * h.rq) * fmaf(m0, r.g2.z, -(m1 * r.g2.y));
-      d = h.d;
     } else {
       // filter branch: rho = 2 |p - c|^2 about the projected centre c, depth m2; its
       // intersection point is the centre's ray at depth m2
       const float im2 = __builtin_amdgcn_rcpf(m2);
       Vr0 = cam.fx * (-2.0f * kFilterScale * h.dx) * im2;
       Vr1 = cam.fy * (-2.0f * kFilterScale * h.dy) * im2;
-      Vd0 = 0.f;
-      Vd1 = 0.f;
-      d = m2;
-    }
-    float xr = xh, yr = yh;
-    if (!h.b3d) {
       xr = ((r.ox + r.g1.x) - cam.cx) * ifx;
       yr = ((r.oy + r.g1.y) - cam.cy) * ify;
     }
+    const float d = h.d;  // m2 in the filter branch
     const float axy = xr * yr, bx = fmaf(xr, xr, 1.0f), by = fmaf(yr, yr, 1.0f);
     const float Vr2 = fmaf(-xr, Vr0, -(yr * Vr1));
-    Vd2 = fmaf(-xr, Vd0, fmaf(-yr, Vd1, 1.0f));
+    const float Vd2 = fmaf(-xr, Vd0, fmaf(-yr, Vd1, 1.0f));
     // J = dalpha/dtau = dLdrho-direction times drho/dalpha = -G o / 2 (unclamped)
     const float jc = h.clamped ? 0.f : -0.5f * h.G * r.c4.x;
     const float jd = jc * d;
@@ -869,31 +983,30 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(5))) voi
   for (int b0 = start; b0 < end; b0 += a.batch) {
     if (__syncthreads_count(!s.done) == 0) break;
     const int nb = min(a.batch, end - b0);
-    for (int k = t; k < nb * kRecF4; k += NT) {
-      const int j = k / kRecF4, f = k - j * kRecF4;
-      const uint32_t id = lds_list ? sid[b0 - start + j] : a.pval[b0 + j];
-      const float4 v = a.rec[(size_t)id * kRecF4 + f];
-      if (f < kLdsRec) srec[j * kLdsRec + f] = v;
-      stage_cull(cull, j, f, v);
-    }
+    stage_records<NT>(srec, a.rec, nb, t, [&](int j) { return lds_list ? sid[b0 - start + j] : a.pval[b0 + j]; },
+                      [](int, uint32_t) {});
     __syncthreads();
-    for (int c0 = 0; c0 < nb; c0 += 64) {
-      if (__ballot(!s.done) == 0ull) break;
-      uint64_t m = overlap_mask(cull, c0, nb, lane, bx0, by0, a.filter, 0, nb);
-      while (m != 0ull) {
-        const int j1 = c0 + __builtin_ctzll(m);
-        m &= m - 1ull;
-        if (!s.done) {
-          const Rec r1 = load_rec(srec, j1);
-          Hit h1;
-          const int k1 = evaluate(fpx, fpy, r1.ox, r1.oy, r1.g1, r1.g2, r1.g3, r1.c4.x, a.z_near, a.filter, h1);
-          if (PROF) {
-            n_eval += 1;
-            n_cov += k1 > 0;
-          }
-          step(k1, h1, r1);
+    const int nc = wave_candidates(srec, nb, lane, bx0, by0, a.filter, 0, nb, list);
+    for (int w0 = 0; w0 < nc; w0 += kWindow) {
+      const uint64_t alive = __ballot(!s.done);
+      if (alive == 0ull) break;
+      const int wn = min(kWindow, nc - w0);
+      uint32_t m = window_mask(srec, list, w0, wn, lane, bx0, by0, rho2_max, alive);
+      // each lane walks its own pixel's candidates
+      if (s.done) m = 0u;
+      int jn = next_entry(list, w0, m);
+      while (m != 0u) {
+        const Rec r1 = load_rec(srec, jn);
+        m &= m - 1u;
+        jn = next_entry(list, w0, m);
+        Hit h1;
+        const int k1 = evaluate(fpx, fpy, r1.ox, r1.oy, r1.g1, r1.g2, r1.g3, r1.c4.x, a.z_near, a.filter, h1);
+        if (PROF) {
+          n_eval += 1;
+          n_cov += k1 > 0;
         }
-        if (__ballot(!s.done) == 0ull) break;
+        step(k1, h1, r1);
+        m = s.done ? 0u : m;
       }
     }
   }
@@ -940,65 +1053,30 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(5))) voi
   }
 }
 
-// Workgroups of `kernel` that fit on the current device at once (occupancy per CU
-// times the CUs), cached per kernel and LDS size: the grid of a persistent launch.
-template <typename K>
-int resident_workgroups(K kernel, int threads, size_t lds) {
-  struct Entry {
-    const void* k;
-    size_t lds;
-    int dev, n;
-  };
-  static std::mutex mu;
-  static std::vector<Entry> cache;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  std::lock_guard<std::mutex> lock(mu);
-  for (const Entry& e : cache)
-    if (e.k == reinterpret_cast<const void*>(kernel) && e.lds == lds && e.dev == dev) return e.n;
-  int per_cu = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return 0;
-  const int n = per_cu * cus;
-  cache.push_back(Entry{reinterpret_cast<const void*>(kernel), lds, dev, n});
-  return n;
-}
-
-// Grid of a blend launch: one workgroup per tile, or with a queue the workgroups that
-// fit at once (each then pulls tiles until the queue is empty; never more than the
-// tiles).  A failed occupancy query falls back to one workgroup per tile.
-template <typename K>
-int blend_grid(const BlendArgs& a, K kernel, int threads, size_t lds) {
-  if (!a.queue) return a.n_tiles;
-  const int n = resident_workgroups(kernel, threads, lds);
-  return n > 0 && n < a.n_tiles ? n : a.n_tiles;
-}
-
 template <int TW, int TH>
 void fwd_shape(const BlendArgs& a, float* t_final, uint32_t* last, unsigned long long* work, hipStream_t s) {
-  // staged records and their cull data, then the staged surfel ids
-  const size_t lds = (size_t)a.batch * ((kLdsRec + 3) * sizeof(float4) + sizeof(uint32_t));
+  // staged records; with contributions also ids and weight sums
+  const size_t lds = (size_t)a.batch * (kRecF4 * sizeof(float4) + (a.contrib ? sizeof(uint64_t) + sizeof(uint32_t) : 0));
   if (work) {
     auto k = blend_fwd_kernel<TW, TH, true>;
-    k<<<blend_grid(a, k, TW * TH, lds), TW * TH, lds, s>>>(a, t_final, last, work);
+    k<<<a.n_tiles, TW * TH, lds, s>>>(a, t_final, last, work);
   } else {
     auto k = blend_fwd_kernel<TW, TH, false>;
-    k<<<blend_grid(a, k, TW * TH, lds), TW * TH, lds, s>>>(a, t_final, last, work);
+    k<<<a.n_tiles, TW * TH, lds, s>>>(a, t_final, last, work);
   }
 }
 
 template <int TW, int TH, bool PO, bool HN, bool HO>
 void bwd_variant(const BlendArgs& a, const float* t_final, const uint32_t* last, float* gacc, float* part,
                  unsigned long long* work, hipStream_t s) {
-  // staged records and their cull data, and in full mode the per-entry term sums
-  const size_t lds = (size_t)a.batch * ((kLdsRec + 3) * sizeof(float4) + (PO ? 0 : 16 * sizeof(float)));
+  // staged records, and in full mode the ids and per-entry term sums
+  const size_t lds = (size_t)a.batch * (kRecF4 * sizeof(float4) + (PO ? 0 : sizeof(uint32_t) + 16 * sizeof(double)));
   if (work) {
     auto k = blend_bwd_kernel<TW, TH, PO, HN, HO, true>;
-    k<<<blend_grid(a, k, TW * TH, lds), TW * TH, lds, s>>>(a, t_final, last, gacc, part, work);
+    k<<<a.n_tiles, TW * TH, lds, s>>>(a, t_final, last, gacc, part, work);
   } else {
     auto k = blend_bwd_kernel<TW, TH, PO, HN, HO, false>;
-    k<<<blend_grid(a, k, TW * TH, lds), TW * TH, lds, s>>>(a, t_final, last, gacc, part, work);
+    k<<<a.n_tiles, TW * TH, lds, s>>>(a, t_final, last, gacc, part, work);
   }
 }
 

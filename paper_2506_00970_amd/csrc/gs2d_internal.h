@@ -140,7 +140,7 @@ struct ViewSet {
   int max_hw = 0;
 };
 
-// Binary search of the view owning item / tile `i` (n_views <= 32).
+// Binary search of the view owning item `i` (n_views <= 32).
 __device__ __forceinline__ int view_of_item(const ViewDesc* v, int nv, int i) {
   int lo = 0;
 #pragma unroll
@@ -148,14 +148,6 @@ __device__ __forceinline__ int view_of_item(const ViewDesc* v, int nv, int i) {
     if (lo + s < nv && v[lo + s].item_base <= i) lo += s;
   return lo;
 }
-__device__ __forceinline__ int view_of_tile(const ViewDesc* v, int nv, int g) {
-  int lo = 0;
-#pragma unroll
-  for (int s = 16; s > 0; s >>= 1)
-    if (lo + s < nv && v[lo + s].tile_base <= g) lo += s;
-  return lo;
-}
-
 }  // namespace gs2d
 
 struct gs2d_ctx {
@@ -188,8 +180,8 @@ struct gs2d_ctx {
 
   // tiles, pixels, partials, view tables
   uint2* ranges = nullptr;
-  uint32_t* queue = nullptr;   // [kQueueOrder + tile_cap]: the blends' work queue
-  bool queue_on = false;       // the last render built the queue (persistent blends)
+  uint32_t* order = nullptr;   // [tile_cap]: tiles by descending list length
+  bool order_on = false;       // the last render built the order (many tiles)
   float* t_final = nullptr;
   uint32_t* last = nullptr;
   float* lgrad = nullptr;      // [4][pixels]: loss gradients of the tracking loop
@@ -307,9 +299,9 @@ void launch_tile_order(const uint2* ranges, int n_tiles, uint32_t* ids, uint32_t
                        const uint32_t* dkey, hipStream_t s);
 void launch_ranges(const uint32_t* skey, Ctrl* ctrl, int64_t p_cap, uint2* ranges, int n_tiles,
                    hipStream_t s);
-// The blends' work queue of a view set: tiles by descending list length (counting
-// order over 64 buckets of 32 entries; within a bucket any order), both heads zero.
-void launch_queue_order(const uint2* ranges, int n_tiles, uint32_t* queue, hipStream_t s);
+// The blends' tile order: tiles by descending list length (counting order over 64
+// buckets of 32 entries; within a bucket any order).
+void launch_length_order(const uint2* ranges, int n_tiles, uint32_t* order, hipStream_t s);
 void launch_copy_u32(const uint32_t* src, uint32_t* dst, int64_t n, hipStream_t s);
 
 struct AdamArgs {  // the tracking pose step's AdamW settings and divergence guard
@@ -352,19 +344,15 @@ struct BlendArgs {
   uint32_t* order_scratch = nullptr;
   const uint32_t* dkey = nullptr;
   const uint32_t* order_keys = nullptr;  // the pairs' depth keys beside order_ids
-  // persistent launch of the forward and backward blends (many more tiles than fit on
-  // the GPU at once): queue[kQueueHeadFwd], queue[kQueueHeadBwd] are the next items,
-  // queue[kQueueOrder + i] the tiles by descending list length; null: one workgroup
-  // per tile
-  uint32_t* queue = nullptr;
+  // forward and backward blends of many more tiles than fit on the GPU at once: workgroup
+  // i blends tile order[i] (descending list length); null: by tile_stride
+  const uint32_t* order = nullptr;
   uint32_t* check = nullptr;  // Ctrl::check_bits (device checks)
+  bool contrib = false;       // forward: some view has a contribution output
 };
 
-constexpr int kQueueHeadFwd = 0;
-constexpr int kQueueHeadBwd = 1;
-constexpr int kQueueOrder = 2;
-// Batched renders with more tiles than this use the persistent blends.
-constexpr int kQueueMinTiles = 4096;
+// Batched renders with more tiles than this take their tiles by descending list length.
+constexpr int kOrderMinTiles = 4096;
 // Tracking: forward blend, tracking loss and pose-only gradient in one walk; needs
 // a.loss_part (tile rows: pose gradient in slots 0-5, loss in slot 6), lambda_d,
 // use_masks, and views with targets.  work: the forward's profile counters.

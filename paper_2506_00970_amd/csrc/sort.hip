@@ -421,38 +421,34 @@ void launch_pass(const PassArgs& a, int grid, hipStream_t s) {
   }
 }
 
-// The blends' work queue: tiles by descending list length.  One workgroup: a
+// The blends' tile order: tiles by descending list length.  One workgroup: a
 // histogram of the lengths over 64 buckets of 32 entries, bucket offsets from the
 // longest bucket down, then each tile's slot by an atomic on its bucket's offset.
-constexpr int kQueueThreads = 1024;
-constexpr int kQueueBuckets = 64;
-__device__ inline int queue_bucket(uint2 r) {
+constexpr int kLengthThreads = 1024;
+constexpr int kLengthBuckets = 64;
+__device__ inline int length_bucket(uint2 r) {
   const uint32_t len = r.y - r.x;
-  return len >= (uint32_t)(32 * (kQueueBuckets - 1)) ? kQueueBuckets - 1 : (int)((len + 31u) >> 5);
+  return len >= (uint32_t)(32 * (kLengthBuckets - 1)) ? kLengthBuckets - 1 : (int)((len + 31u) >> 5);
 }
-__global__ __launch_bounds__(kQueueThreads) void queue_order_kernel(const uint2* __restrict__ ranges, int n_tiles,
-                                                                    uint32_t* __restrict__ queue) {
-  __shared__ uint32_t hist[kQueueBuckets], off[kQueueBuckets];
+__global__ __launch_bounds__(kLengthThreads) void length_order_kernel(const uint2* __restrict__ ranges, int n_tiles,
+                                                                    uint32_t* __restrict__ order) {
+  __shared__ uint32_t hist[kLengthBuckets], off[kLengthBuckets];
   const int t = threadIdx.x;
-  if (t < kQueueBuckets) hist[t] = 0u;
-  if (t == 0) {
-    queue[kQueueHeadFwd] = 0u;
-    queue[kQueueHeadBwd] = 0u;
-  }
+  if (t < kLengthBuckets) hist[t] = 0u;
   __syncthreads();
-  for (int i = t; i < n_tiles; i += kQueueThreads) atomicAdd(&hist[queue_bucket(ranges[i])], 1u);
+  for (int i = t; i < n_tiles; i += kLengthThreads) atomicAdd(&hist[length_bucket(ranges[i])], 1u);
   __syncthreads();
   if (t == 0) {
     uint32_t run = 0u;
-    for (int b = kQueueBuckets - 1; b >= 0; --b) {
+    for (int b = kLengthBuckets - 1; b >= 0; --b) {
       off[b] = run;
       run += hist[b];
     }
   }
   __syncthreads();
-  for (int i = t; i < n_tiles; i += kQueueThreads) {
-    const uint32_t pos = atomicAdd(&off[queue_bucket(ranges[i])], 1u);
-    queue[kQueueOrder + pos] = (uint32_t)i;
+  for (int i = t; i < n_tiles; i += kLengthThreads) {
+    const uint32_t pos = atomicAdd(&off[length_bucket(ranges[i])], 1u);
+    order[pos] = (uint32_t)i;
   }
 }
 
@@ -544,8 +540,8 @@ void launch_ranges(const uint32_t* skey, Ctrl* ctrl, int64_t p_cap, uint2* range
   ranges_kernel<<<blocks_for(p_cap, 256), 256, 0, s>>>(skey, ctrl, p_cap, ranges, n_tiles);
 }
 
-void launch_queue_order(const uint2* ranges, int n_tiles, uint32_t* queue, hipStream_t s) {
-  queue_order_kernel<<<1, kQueueThreads, 0, s>>>(ranges, n_tiles, queue);
+void launch_length_order(const uint2* ranges, int n_tiles, uint32_t* order, hipStream_t s) {
+  length_order_kernel<<<1, kLengthThreads, 0, s>>>(ranges, n_tiles, order);
 }
 
 void launch_tile_order(const uint2* ranges, int n_tiles, uint32_t* ids, uint32_t* scratch, const uint32_t* pdk,
