@@ -114,29 +114,11 @@ int stream_capturing(hipStream_t s, bool* cap) {
   return 0;
 }
 
-int ensure_hist(gs2d_ctx* ctx) {
-  const int64_t items = ctx->n_cap > ctx->p_cap ? ctx->n_cap : ctx->p_cap;
-  // two planes of 2048 digit rows by one column per block, plus the row totals
-  const int64_t stride = (items + kScanItems - 1) / kScanItems > 0 ? (items + kScanItems - 1) / kScanItems : 1;
-  if (stride <= ctx->hist_stride) return GS2D_OK;
-  const int64_t need = 2 * stride * (1 << kMaxDigitBits) + (1 << kMaxDigitBits);
-  GS2D_TRY(realloc_dev(ctx, &ctx->hist, need));
-  ctx->hist_cap = need;
-  ctx->hist_stride = (int)stride;
-  ctx->hist_fresh = true;  // cleared on the stream before its first use
-  return GS2D_OK;
-}
-
-SortPlanes sort_planes(gs2d_ctx* ctx) {
-  const size_t plane = (size_t)ctx->hist_stride << kMaxDigitBits;
-  return SortPlanes{{ctx->hist, ctx->hist + plane}, ctx->hist_stride, ctx->hist + 2 * plane};
-}
-
-// The sort planes must be all zero before a render; fresh allocations are cleared here.
-void clear_fresh_hist(gs2d_ctx* ctx, hipStream_t s) {
-  if (!ctx->hist_fresh) return;
-  launch_fill_u32(ctx->hist, 0u, ctx->hist_cap, s);
-  ctx->hist_fresh = false;
+// The tile counters must be all zero before a render; a fresh allocation is cleared here.
+void clear_fresh_counts(gs2d_ctx* ctx, hipStream_t s) {
+  if (!ctx->tcount_fresh) return;
+  launch_fill_u32(ctx->tcount, 0u, ctx->tile_cap * kCountStride, s);
+  ctx->tcount_fresh = false;
 }
 
 int ensure_surfels(gs2d_ctx* ctx, int64_t n) {
@@ -148,23 +130,22 @@ int ensure_surfels(gs2d_ctx* ctx, int64_t n) {
   GS2D_TRY(realloc_dev(ctx, &ctx->dkey, cap));
   GS2D_TRY(realloc_dev(ctx, &ctx->parts, 2 * (cap / kPartItems + 1)));
   ctx->n_cap = cap;
-  return ensure_hist(ctx);
+  return GS2D_OK;
 }
 
 int ensure_pairs(gs2d_ctx* ctx, int64_t p) {
   if (p <= ctx->p_cap) return GS2D_OK;
   const int64_t cap = round_up(p, kScanItems);
-  for (int k = 0; k < 2; ++k) {
-    GS2D_TRY(realloc_dev(ctx, &ctx->pkey[k], cap));
-    GS2D_TRY(realloc_dev(ctx, &ctx->pval[k], cap));
-    GS2D_TRY(realloc_dev(ctx, &ctx->pdk[k], cap));
-  }
+  ctx->p_cap = 0;  // (an allocation that fails leaves no pair buffers)
+  GS2D_TRY(realloc_dev(ctx, &ctx->pairs, cap));
+  GS2D_TRY(realloc_dev(ctx, &ctx->placed, cap));
+  GS2D_TRY(realloc_dev(ctx, &ctx->ids, cap));
   if (ctx->opt.keep_unsorted) {
     GS2D_TRY(realloc_dev(ctx, &ctx->pkey_keep, cap));
     GS2D_TRY(realloc_dev(ctx, &ctx->pval_keep, cap));
   }
   ctx->p_cap = cap;
-  return ensure_hist(ctx);
+  return GS2D_OK;
 }
 
 int ensure_pixels(gs2d_ctx* ctx, int64_t hw) {
@@ -179,6 +160,8 @@ int ensure_tiles(gs2d_ctx* ctx, int64_t tiles) {
   if (tiles <= ctx->tile_cap) return GS2D_OK;
   GS2D_TRY(realloc_dev(ctx, &ctx->ranges, tiles));
   GS2D_TRY(realloc_dev(ctx, &ctx->order, tiles));
+  GS2D_TRY(realloc_dev(ctx, &ctx->tcount, tiles * kCountStride));
+  ctx->tcount_fresh = true;  // cleared on the stream before its first use
   ctx->tile_cap = tiles;
   return GS2D_OK;
 }
@@ -196,12 +179,6 @@ int ensure_gacc(gs2d_ctx* ctx, int64_t n) {
   GS2D_TRY(realloc_dev(ctx, &ctx->gacc, cap * 16));
   ctx->gacc_cap = cap;
   return GS2D_OK;
-}
-
-int tile_bits(int n_tiles) {
-  int b = 1;
-  while ((1 << b) < n_tiles) ++b;
-  return b;
 }
 
 bool valid_tile(int tw, int th) {
@@ -279,8 +256,8 @@ int tile_stride(int64_t n) {
   return s;
 }
 
-BlendArgs blend_args(gs2d_ctx* ctx, const ViewSet& vs, int pair_buf) {
-  BlendArgs a{ctx->ranges, ctx->pval[pair_buf], ctx->rec, ctx->views, vs.n_views,
+BlendArgs blend_args(gs2d_ctx* ctx, const ViewSet& vs) {
+  BlendArgs a{ctx->ranges, ctx->ids, ctx->rec, ctx->views, vs.n_views,
               (int)vs.tiles, ctx->opt.z_near, ctx->opt.filter, ctx->opt.batch};
   a.tile_stride = tile_stride(vs.tiles);
   a.order = ctx->order_on ? ctx->order : nullptr;
@@ -327,7 +304,6 @@ int render_views(gs2d_ctx* ctx, const ViewSet& vs, hipStream_t s, bool allow_syn
     GS2D_TRY(ensure_pairs(ctx, ctx->opt.pair_capacity > 0 ? ctx->opt.pair_capacity : 4 * (items > 0 ? items : 1)));
   if (upload) launch_upload_views(vs, ctx->views, s, ctx->ctrl);
   const int tw = ctx->opt.tile_w, th = ctx->opt.tile_h;
-  int pbuf = 0;
   if (items == 0) {
     for (int k = 0; k < nv; ++k) {
       const ViewDesc& d = vs.v[k];
@@ -343,8 +319,7 @@ int render_views(gs2d_ctx* ctx, const ViewSet& vs, hipStream_t s, bool allow_syn
     launch_fill_u32(reinterpret_cast<uint32_t*>(ctx->ctrl), 0u, 3, s);
     ctx->order_on = false;
   } else {
-    clear_fresh_hist(ctx, s);
-    SortPlanes ws = sort_planes(ctx);
+    clear_fresh_counts(ctx, s);
     uint32_t* part_pairs = ctx->parts;
     uint32_t* part_vis = ctx->parts + ctx->n_cap / kPartItems + 1;
     {
@@ -362,15 +337,10 @@ int render_views(gs2d_ctx* ctx, const ViewSet& vs, hipStream_t s, bool allow_syn
       ProfScope ps(ctx, kScan, s);
       launch_part_scan(part_pairs, part_vis, items, ctx->ctrl, np_out, s);
     }
-    // pairs in item order; a tile sort of one pass (up to 2048 tiles) writes the tile
-    // ranges itself
-    const int tbits = tile_bits((int)vs.tiles);
-    const bool fused_ranges = tbits <= kMaxDigitBits;
     auto duplicate = [&](uint32_t* np_dst) {
       ProfScope ps(ctx, kDup, s);
-      launch_duplicate(ws, ctx->count, part_pairs, part_vis, scanned, ctx->rect, ctx->views, nv, items, ctx->p_cap,
-                       tbits, ctx->pkey[0], ctx->pval[0], ctx->ctrl, ctx->ranges, (int)vs.tiles, ctx->dkey,
-                       ctx->pdk[0], np_dst, s);
+      launch_duplicate(ctx->count, part_pairs, part_vis, scanned, ctx->rect, ctx->views, nv, items, ctx->p_cap,
+                       ctx->dkey, ctx->pairs, ctx->tcount, (int)vs.tiles, ctx->ctrl, np_dst, s);
     };
     duplicate(np_out);
     if (read_np) {
@@ -391,42 +361,32 @@ int render_views(gs2d_ctx* ctx, const ViewSet& vs, hipStream_t s, bool allow_syn
       ctx->host_ctrl->n_pairs = np32;  // for callers that size buffers from this render
       if (np > ctx->p_cap) {
         GS2D_HIP(ctx, hipStreamSynchronize(s));
-        // grow and duplicate again (the first pass counted part of its pairs into plane 1)
+        // grow and duplicate again (the first pass counted part of its pairs)
+        ctx->tcount_fresh = true;
         GS2D_TRY(ensure_pairs(ctx, np + np / 4));
-        if (ctx->hist_fresh) {
-          clear_fresh_hist(ctx, s);
-        } else {
-          launch_fill_u32(ctx->hist + ((size_t)ctx->hist_stride << kMaxDigitBits), 0u,
-                          (int64_t)ctx->hist_stride << kMaxDigitBits, s);
-        }
-        ws = sort_planes(ctx);
+        clear_fresh_counts(ctx, s);
         launch_fill_u32(&ctx->ctrl->overflow, 0u, 1, s);  // set by the first pass
         duplicate(nullptr);
       }
     }
-    if (ctx->opt.keep_unsorted && ctx->pkey_keep) {
-      launch_copy_u32(ctx->pkey[0], ctx->pkey_keep, ctx->p_cap, s);
-      launch_copy_u32(ctx->pval[0], ctx->pval_keep, ctx->p_cap, s);
+    if (ctx->opt.keep_unsorted && ctx->pkey_keep)
+      launch_split_pairs(ctx->pairs, ctx->p_cap, ctx->pkey_keep, ctx->pval_keep, s);
+    // many more tiles than fit on the GPU at once: the blends take the longest lists first
+    ctx->order_on = blend && vs.tiles > kOrderMinTiles;
+    {
+      ProfScope ps(ctx, kRanges, s);
+      launch_ranges(ctx->tcount, (int)vs.tiles, ctx->ctrl, ctx->ranges, ctx->order_on ? ctx->order : nullptr, s);
     }
     {
       ProfScope ps(ctx, kTileSort, s);
-      pbuf = tile_sort(ws, ctx->pkey, ctx->pval, ctx->pdk, ctx->p_cap, tbits, ctx->ctrl, ctx->ranges, (int)vs.tiles,
-                       s);
-    }
-    if (!fused_ranges) {
-      ProfScope ps(ctx, kRanges, s);
-      launch_ranges(ctx->pkey[pbuf], ctx->ctrl, ctx->p_cap, ctx->ranges, (int)vs.tiles, s);
+      launch_place(ctx->pairs, ctx->ctrl, ctx->p_cap, ctx->ranges, (int)vs.tiles, ctx->placed, s);
     }
     if (order) {
-      // each tile's items, ascending on entry, stably into depth order
+      // each tile's pairs into depth order
       ProfScope ps(ctx, kDepthSort, s);
-      launch_tile_order(ctx->ranges, (int)vs.tiles, ctx->pval[pbuf], ctx->pval[pbuf ^ 1], ctx->pdk[pbuf], ctx->dkey,
-                        s);
+      launch_tile_order(ctx->ranges, (int)vs.tiles, ctx->placed, reinterpret_cast<uint64_t*>(ctx->pairs), ctx->ids, s);
     }
-    // many more tiles than fit on the GPU at once: the blends take the longest lists first
-    ctx->order_on = blend && vs.tiles > kOrderMinTiles;
-    if (ctx->order_on) launch_length_order(ctx->ranges, (int)vs.tiles, ctx->order, s);
-    BlendArgs ba = blend_args(ctx, vs, pbuf);
+    BlendArgs ba = blend_args(ctx, vs);
     if (ro) {
       ba.res_x = ro->x;
       ba.res_part = ro->part;
@@ -445,7 +405,6 @@ int render_views(gs2d_ctx* ctx, const ViewSet& vs, hipStream_t s, bool allow_syn
   GS2D_HIP(ctx, hipGetLastError());
   ctx->generation += 1;
   ctx->last_views = vs;
-  ctx->pair_buf = pbuf;
   ctx->have_forward = true;
   return GS2D_OK;
 }
@@ -480,7 +439,7 @@ int backward_views(gs2d_ctx* ctx, const gs2d_view_grad* grads, int nv, int acc, 
     GS2D_TRY(ensure_gacc(ctx, vs.items));
   }
   launch_upload_views(vs, ctx->views, s);
-  const BlendArgs ba = blend_args(ctx, vs, ctx->pair_buf);
+  const BlendArgs ba = blend_args(ctx, vs);
   if (!full) {
     {
       ProfScope ps(ctx, kBlendBwd, s);
@@ -648,15 +607,14 @@ int track_iteration(gs2d_ctx* ctx, const ViewSet& vs, const gs2d_track_args* a, 
   GS2D_TRY(render_views(ctx, vs, s, false, false, nullptr, false, !walk_orders, true));
   const int stride = loss_blocks(vs.max_hw);
   if (vs.items > 0) {
-    BlendArgs ba = blend_args(ctx, vs, ctx->pair_buf);
+    BlendArgs ba = blend_args(ctx, vs);
     ba.loss_part = ctx->part;
     ba.lambda_d = a->lambda_d;
     ba.use_masks = a->use_masks;
     if (walk_orders) {
-      ba.order_ids = ctx->pval[ctx->pair_buf];
-      ba.order_scratch = ctx->pval[ctx->pair_buf ^ 1];
-      ba.dkey = ctx->dkey;
-      ba.order_keys = ctx->pdk[ctx->pair_buf];
+      ba.order_pairs = ctx->placed;
+      ba.order_scratch = reinterpret_cast<uint64_t*>(ctx->pairs);
+      ba.order_ids = ctx->ids;
     }
     ProfScope ps(ctx, kBlendTrack, s);
     launch_blend_track(ba, ctx->opt.tile_w, ctx->opt.tile_h, work_ptr(ctx, s), s);
@@ -905,11 +863,11 @@ GS2D_API int gs2d_destroy(gs2d_ctx* ctx) {
   if (!ctx) return GS2D_OK;
   (void)set_device(ctx);
   invalidate_graph(ctx);
-  void* bufs[] = {ctx->rec,       ctx->rect,       ctx->count,     ctx->dkey,      ctx->parts,     ctx->hist,
-                  ctx->gacc,      ctx->pkey[0],    ctx->pkey[1],   ctx->pval[0],   ctx->pval[1],   ctx->pkey_keep,
+  void* bufs[] = {ctx->rec,       ctx->rect,       ctx->count,     ctx->dkey,      ctx->parts,     ctx->tcount,
+                  ctx->gacc,      ctx->pairs,      ctx->placed,    ctx->ids,       ctx->pkey_keep,
                   ctx->pval_keep, ctx->ranges,     ctx->t_final,   ctx->last,      ctx->lgrad,     ctx->limg,
                   ctx->part,      ctx->lpart,      ctx->pose0,     ctx->saved_pose, ctx->views,    ctx->ctrl,
-                  ctx->order,     ctx->pdk[0],     ctx->pdk[1]};
+                  ctx->order};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   if (ctx->host_ctrl) (void)hipHostFree(ctx->host_ctrl);
@@ -1185,8 +1143,8 @@ GS2D_API int gs2d_debug_copy(gs2d_ctx* ctx, int32_t which, void* host_dst, size_
   size_t need = 0;
   const int64_t np = c.n_pairs < ctx->p_cap ? c.n_pairs : ctx->p_cap;
   switch (which) {
-    case 0: src = ctx->pkey[ctx->pair_buf]; need = (size_t)np * 4; break;
-    case 1: src = ctx->pval[ctx->pair_buf]; need = (size_t)np * 4; break;
+    case 0: src = ctx->ranges; need = (size_t)np * 4; break;  // (each tile's index over its range, below)
+    case 1: src = ctx->ids; need = (size_t)np * 4; break;
     case 2: src = ctx->ranges; need = (size_t)ctx->last_views.tiles * 8; break;
     case 3: src = ctx->dkey; need = (size_t)items * 4; break;
     case 4: src = ctx->rect; need = (size_t)items * 8; break;
@@ -1201,7 +1159,16 @@ GS2D_API int gs2d_debug_copy(gs2d_ctx* ctx, int32_t which, void* host_dst, size_
     *bytes = need;
     return GS2D_ERR_INVALID_ARG;
   }
-  if (need > 0) GS2D_HIP(ctx, hipMemcpy(host_dst, src, need, hipMemcpyDeviceToHost));
+  if (need > 0 && which == 0) {
+    std::vector<uint2> rg((size_t)ctx->last_views.tiles);
+    GS2D_HIP(ctx, hipMemcpy(rg.data(), src, rg.size() * sizeof(uint2), hipMemcpyDeviceToHost));
+    std::memset(host_dst, 0, need);
+    uint32_t* keys = static_cast<uint32_t*>(host_dst);
+    for (size_t t = 0; t < rg.size(); ++t)
+      for (uint32_t e = rg[t].x; e < rg[t].y && (int64_t)e < np; ++e) keys[e] = (uint32_t)t;
+  } else if (need > 0) {
+    GS2D_HIP(ctx, hipMemcpy(host_dst, src, need, hipMemcpyDeviceToHost));
+  }
   *bytes = need;
   return GS2D_OK;
 }

@@ -847,11 +847,11 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(4))) voi
   blend_bwd_tile<TW, TH, POSE_ONLY, HAS_N, HAS_O, PROF>(a, grid_tile(a), t_final, last_in, gacc, part, work);
 }
 
-// float4 slots before the ordered list in the tracking walk's LDS: the staged records,
-// or the ordering's scratch, whichever is larger (both are used
-// one after the other)
-__host__ __device__ constexpr int track_stage_f4(int batch) {
-  return batch * kRecF4 > (kOrderScratchWords + 3) / 4 ? batch * kRecF4 : (kOrderScratchWords + 3) / 4;
+// The tracking walk's LDS, in float4: the staged records, then the ordered list; before
+// the walk, the ordering's keys over both (the list is written once they have been read).
+__host__ __device__ constexpr int track_lds_f4(int batch) {
+  constexpr int keys = kOrderMax * 8 / 16, list = kOrderMax * 4 / 16;
+  return batch * kRecF4 + list > keys ? batch * kRecF4 + list : keys;
 }
 
 // Tracking: the forward blend, the tracking loss and the pose-only gradient in one
@@ -893,12 +893,12 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(5))) voi
   prioritise(end - start);
   // the tile's depth order, in LDS when the list fits (see tile_order.h); the staged
   // records are then gathered through the ordered ids in LDS
-  uint32_t* const sid = reinterpret_cast<uint32_t*>(srec + track_stage_f4(a.batch));
+  uint32_t* const sid = reinterpret_cast<uint32_t*>(srec + a.batch * kRecF4);
   bool lds_list = false;
   if constexpr (NT == kBlockThreads) {
-    if (a.order_ids)
-      lds_list = order_list(a.order_ids, a.order_scratch, a.dkey, start, end - start,
-                            order_lds(reinterpret_cast<uint32_t*>(srec), sid), false, a.order_keys);
+    if (a.order_pairs)
+      lds_list = order_list(a.order_pairs, a.order_scratch, a.order_ids, start, end - start,
+                            reinterpret_cast<uint64_t*>(srec), sid, false);
   }
   FwdPix s{1.0f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0, !inside};
   float Q[6], Ar[6], Ag[6], Ab[6], AD[6];
@@ -983,8 +983,10 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(5))) voi
   for (int b0 = start; b0 < end; b0 += a.batch) {
     if (__syncthreads_count(!s.done) == 0) break;
     const int nb = min(a.batch, end - b0);
-    stage_records<NT>(srec, a.rec, nb, t, [&](int j) { return lds_list ? sid[b0 - start + j] : a.pval[b0 + j]; },
-                      [](int, uint32_t) {});
+    if (lds_list)
+      stage_records<NT>(srec, a.rec, nb, t, [&](int j) { return sid[b0 - start + j]; }, [](int, uint32_t) {});
+    else
+      stage_records<NT>(srec, a.rec, nb, t, [&](int j) { return a.pval[b0 + j]; }, [](int, uint32_t) {});
     __syncthreads();
     const int nc = wave_candidates(srec, nb, lane, bx0, by0, a.filter, 0, nb, list);
     for (int w0 = 0; w0 < nc; w0 += kWindow) {
@@ -1111,8 +1113,7 @@ void launch_blend_fwd(const BlendArgs& a, int tile_w, int tile_h, float* t_final
 
 template <int TW, int TH>
 void track_shape(const BlendArgs& a, unsigned long long* work, hipStream_t s) {
-  // staging (or, before it, the ordering's scratch), then the ordered list
-  const size_t lds = (size_t)track_stage_f4(a.batch) * sizeof(float4) + kOrderMax * sizeof(uint32_t);
+  const size_t lds = (size_t)track_lds_f4(a.batch) * sizeof(float4);
   if (work)
     blend_track_kernel<TW, TH, true><<<a.n_tiles, TW * TH, lds, s>>>(a, work);
   else

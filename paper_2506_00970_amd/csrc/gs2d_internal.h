@@ -165,21 +165,19 @@ struct gs2d_ctx {
   uint32_t* count = nullptr;
   uint32_t* dkey = nullptr;     // per-item depth keys
   uint32_t* parts = nullptr;   // per-block pair and visible counts of preprocessing
-  uint32_t* hist = nullptr;    // the sort planes and row totals (gs2d::SortPlanes)
-  int64_t hist_cap = 0;
-  int hist_stride = 0;
-  bool hist_fresh = false;     // allocated but not yet cleared on the stream
   float* gacc = nullptr;       // [items][16]
 
   // pairs [p_cap]
-  uint32_t* pkey[2] = {nullptr, nullptr};
-  uint32_t* pval[2] = {nullptr, nullptr};
-  uint32_t* pdk[2] = {nullptr, nullptr};  // each pair's depth key, moved with pval by the tile sort
+  uint4* pairs = nullptr;      // as emitted: (tile, item, depth key, place within the tile); later scratch
+  uint64_t* placed = nullptr;  // by tile: (depth key << 32 | item)
+  uint32_t* ids = nullptr;     // by tile, in depth order: the lists that the blends walk
   uint32_t* pkey_keep = nullptr;
   uint32_t* pval_keep = nullptr;
 
   // tiles, pixels, partials, view tables
   uint2* ranges = nullptr;
+  uint32_t* tcount = nullptr;  // [tile_cap * kCountStride]: pairs per tile, all zero between renders
+  bool tcount_fresh = false;   // allocated but not yet cleared on the stream
   uint32_t* order = nullptr;   // [tile_cap]: tiles by descending list length
   bool order_on = false;       // the last render built the order (many tiles)
   float* t_final = nullptr;
@@ -221,7 +219,6 @@ struct gs2d_ctx {
   // state of the last render
   uint32_t generation = 0;
   gs2d::ViewSet last_views;    // views of the last render (host copy)
-  int pair_buf = 0;            // which pkey/pval holds the sorted pairs
   bool have_forward = false;
 };
 
@@ -255,20 +252,14 @@ int launch_preprocess_bwd_group(const float* params, int n, int n_views, const f
                                 int accumulate, float* part, hipStream_t s);
 
 // sort.hip
-constexpr int kScanItems = 1024;   // keys per block of the radix passes
-constexpr int kMaxDigitBits = 11;  // widest radix digit (2048 bins)
+constexpr int kScanItems = 1024;  // the per-item and per-pair buffers grow in these steps
+// Words from one tile's counter to the next: the counters that one cache line holds share
+// its atomics' throughput (one per 6.7 ns).  The duplication and the range scan of an
+// eight-view window take 409, 220, 192, 175 and 176 us at 1, 4, 8, 16 and 32 words, of five
+// 640 x 480 views 89, 54, 51, 57 and 61.
+constexpr int kCountStride = 16;
 void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 void launch_fill_f32(float* p, float v, int64_t n, hipStream_t s);
-// Digit histograms of the tile sort's passes: two digit-major planes of 2048 rows by
-// `stride` columns (one per block of kScanItems pairs) and the row totals.  Between
-// renders both planes are all zero.
-struct SortPlanes {
-  uint32_t* plane[2];
-  int stride;
-  uint32_t* dtot;
-};
-// Bits of pass p of a stable LSD sort over `bits` key bits in passes of at most 11.
-int radix_pass_bits(int bits, int p);
 // Whether `items` take the scan below (many preprocessing blocks); otherwise the
 // duplication sums the per-block counts itself.
 bool part_scan_needed(int64_t items);
@@ -276,33 +267,27 @@ bool part_scan_needed(int64_t items);
 // (n_pairs also to *np_host, a host-visible word, if not NULL).
 void launch_part_scan(uint32_t* part_pairs, const uint32_t* part_vis, int64_t items, Ctrl* ctrl, uint32_t* np_host,
                       hipStream_t s);
-// The (tile, item) pairs of every item, in item order, placed by the per-block pair
-// counts of preprocessing (an exclusive prefix when `scanned`; otherwise the kernel
-// also stores ctrl->n_pairs, and *np_host if not NULL, and ctrl->n_visible); sets
-// ctrl->overflow when the pairs exceed p_cap.  Fills plane 1 with the first tile
-// pass's histogram.  Each pair's depth key (dkey of its item) goes to pdk beside pval.
-void launch_duplicate(const SortPlanes& ws, const uint32_t* count, const uint32_t* part_pairs,
-                      const uint32_t* part_vis, bool scanned, const uint2* rect, const ViewDesc* views, int n_views,
-                      int64_t items, int64_t p_cap, int tile_bits, uint32_t* pkey, uint32_t* pval, Ctrl* ctrl,
-                      uint2* ranges, int n_tiles, const uint32_t* dkey, uint32_t* pdk, uint32_t* np_host,
-                      hipStream_t s);
-// Stable sort of the min(n_pairs, p_cap) pairs by tile key over `bits` bits, moving
-// vals and dks with the keys.  A single pass also writes the tile ranges (empty after
-// an overflow).  Returns the buffer index.
-int tile_sort(const SortPlanes& ws, uint32_t* keys[2], uint32_t* vals[2], uint32_t* dks[2], int64_t p_cap, int bits,
-              Ctrl* ctrl, uint2* ranges, int n_tiles, hipStream_t s);
-// Orders every tile's items (ids[ranges[t].x .. ranges[t].y), ascending on entry) by
-// depth key, stably: each list then ascends in (depth key, item).  pdk: the pairs'
-// depth keys beside ids; scratch: a buffer of the same size as ids for lists longer
-// than one workgroup's LDS (those read the keys through dkey[id]).
-void launch_tile_order(const uint2* ranges, int n_tiles, uint32_t* ids, uint32_t* scratch, const uint32_t* pdk,
-                       const uint32_t* dkey, hipStream_t s);
-void launch_ranges(const uint32_t* skey, Ctrl* ctrl, int64_t p_cap, uint2* ranges, int n_tiles,
-                   hipStream_t s);
-// The blends' tile order: tiles by descending list length (counting order over 64
-// buckets of 32 entries; within a bucket any order).
-void launch_length_order(const uint2* ranges, int n_tiles, uint32_t* order, hipStream_t s);
-void launch_copy_u32(const uint32_t* src, uint32_t* dst, int64_t n, hipStream_t s);
+// The pairs of every item, in item order, placed by the per-block pair counts of
+// preprocessing (an exclusive prefix when `scanned`; otherwise the kernel also stores
+// ctrl->n_pairs, and *np_host if not NULL, and ctrl->n_visible); sets ctrl->overflow when
+// the pairs exceed p_cap.  tcount (zero on entry) counts the pairs per tile.
+void launch_duplicate(const uint32_t* count, const uint32_t* part_pairs, const uint32_t* part_vis, bool scanned,
+                      const uint2* rect, const ViewDesc* views, int n_views, int64_t items, int64_t p_cap,
+                      const uint32_t* dkey, uint4* pairs, uint32_t* tcount, int n_tiles, Ctrl* ctrl,
+                      uint32_t* np_host, hipStream_t s);
+// The tile ranges (empty after an overflow) from the counters, which are zero again
+// afterwards; with `order` (nullable) also the tiles by descending list length (counting
+// order over 64 buckets of 32 entries; within a bucket any order).
+void launch_ranges(uint32_t* tcount, int n_tiles, Ctrl* ctrl, uint2* ranges, uint32_t* order, hipStream_t s);
+// The pairs as (depth key << 32 | item) in their tiles' ranges, in any order within each.
+void launch_place(const uint4* pairs, Ctrl* ctrl, int64_t p_cap, const uint2* ranges, int n_tiles, uint64_t* placed,
+                  hipStream_t s);
+// Orders every tile's pairs by (depth key, item) into ids; placed and scratch (of the
+// same size, for lists longer than one workgroup's LDS) are overwritten.
+void launch_tile_order(const uint2* ranges, int n_tiles, uint64_t* placed, uint64_t* scratch, uint32_t* ids,
+                       hipStream_t s);
+// The tile keys and items of n pairs as emitted.
+void launch_split_pairs(const uint4* pairs, int64_t n, uint32_t* key, uint32_t* id, hipStream_t s);
 
 struct AdamArgs {  // the tracking pose step's AdamW settings and divergence guard
   float lr[6];
@@ -337,13 +322,12 @@ struct BlendArgs {
   // over the block in res_part[block]
   uint16_t* res_x = nullptr;
   float* res_part = nullptr;
-  // tracking walk with 256-thread tiles: with order_ids, each workgroup first orders
-  // its own tile's list (order_ids = the tile-sorted ids, order_scratch a buffer of the
-  // same size, dkey the per-item depth keys), so no separate depth-order kernel runs
+  // tracking walk with 256-thread tiles: with order_pairs (the placed pairs), each
+  // workgroup first orders its own tile's list, so no separate depth-order kernel runs
+  // (lists longer than its LDS into order_ids = pval, through order_scratch)
+  uint64_t* order_pairs = nullptr;
+  uint64_t* order_scratch = nullptr;
   uint32_t* order_ids = nullptr;
-  uint32_t* order_scratch = nullptr;
-  const uint32_t* dkey = nullptr;
-  const uint32_t* order_keys = nullptr;  // the pairs' depth keys beside order_ids
   // forward and backward blends of many more tiles than fit on the GPU at once: workgroup
   // i blends tile order[i] (descending list length); null: by tile_stride
   const uint32_t* order = nullptr;
