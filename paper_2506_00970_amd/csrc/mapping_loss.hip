@@ -6,19 +6,29 @@
 // (eq:normal_fromD): normalised cross product of the central differences of the
 // back-projected pixels, 0 on the image border and where the cross product vanishes.
 //
-// Two kernels over 16 x 16 pixel tiles with a 5-pixel halo staged in LDS, one colour
-// channel at a time:
-//  * forward: the 15 windowed statistics of each pixel by a horizontal then a
-//    vertical pass, in FP64: the variances E[x^2] - mu^2 cancel in flat regions,
-//    and the gradient that follows cancels again, so FP32 statistics leave it only a
-//    few bits; SSIM and its per-pixel adjoint coefficients A, B, C (so that
-//    dL/dI_r = W*A + 2 I_r (W*B) + I (W*C)); the depth normal, d_normal, and the
-//    gradients to the two neighbour differences; one partial of each loss term per
-//    workgroup.
+// Two kernels over 16 x 48 pixel tiles with a 5-pixel halo staged in LDS, one colour
+// channel per workgroup:
+//  * forward: the windowed statistics of each pixel by a horizontal then a vertical
+//    pass, in FP64: the variances E[x^2] - mu^2 cancel in flat regions, and the gradient
+//    that follows cancels again, so FP32 statistics leave it only a few bits; SSIM and its
+//    per-pixel adjoint coefficients A, B, C (so that dL/dI_r = W*A + 2 I_r (W*B) +
+//    I (W*C)); the depth normal, d_normal, and the gradients to the two neighbour
+//    differences; one partial of each loss term per workgroup.
 //  * backward: the window filter of A, B, C (the Gaussian is symmetric, so the adjoint
 //    of the zero-padded filter is the same filter), d_rgb and, gathering the
 //    neighbour-difference gradients of the 4 neighbours, d_depth.  Workgroup 0 also
 //    adds the forward's partials in a fixed order.
+//
+// The forward is bound by FP64 issue (VALU busy 75 %), the backward by the latency of its
+// loads and the planes' traffic.  Each thread filters runs: four neighbouring outputs of a
+// row from 14 inputs, three of a column from 13, so an input is read (and its products
+// formed) once per run instead of once per output; a tall tile has less halo in the
+// horizontal pass (58 rows for 48 outputs, against 26 for 16); one channel per workgroup,
+// with the depth and normal terms in workgroups of their own, makes enough workgroups for
+// the chip and few round trips to memory in each; and neighbouring tiles share an XCD.
+// At 1200 x 680: forward 61 -> 38 us, backward 45 -> 23 (39 before the XCD mapping); at
+// 640 x 480: 28 -> 17 and 20 -> 12 (from one output per thread, 16 x 16 tiles in
+// row-major order and the channels in turn).  Tiles of 32 rows: 44 and 23, 20 and 11.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -30,10 +40,19 @@ namespace gs2d {
 namespace maploss {
 namespace {
 
-constexpr int kT = 16;              // output tile side
-constexpr int kR = 5;               // window radius
-constexpr int kS = kT + 2 * kR;     // staged side, 26
-constexpr int kThreads = kT * kT;   // one thread per output pixel
+constexpr int kR = 5;                // window radius
+constexpr int kTaps = 2 * kR + 1;
+constexpr int kTW = 16, kTH = 48;    // output tile
+constexpr int kSW = kTW + 2 * kR;    // staged width, 26
+constexpr int kSP = 28;              // its pitch: runs start 16-byte aligned
+constexpr int kSH = kTH + 2 * kR;    // staged rows, 58
+constexpr int kRun = 4;              // neighbouring outputs per thread of the horizontal pass
+constexpr int kRuns = kTW / kRun;
+constexpr int kThreads = 256;
+constexpr int kXcds = 8;
+constexpr int kStats = 4;  // x, y, x^2 + y^2 (SSIM takes the variances' sum only), xy
+constexpr int kRows = kTW * kTH / kThreads;  // outputs per thread of the vertical pass, one column
+static_assert(kRows * kThreads == kTW * kTH && kSH * kRuns <= kThreads, "tile");
 constexpr double kC1 = 0.01 * 0.01;
 constexpr double kC2 = 0.03 * 0.03;
 
@@ -53,7 +72,7 @@ struct Args {
   float* d_normal;
   float* coef;   // 9 planes: A (3 channels), B (3), C (3)
   float* gdiff;  // 6 planes: dL/d(dx) (3), dL/d(dy) (3)
-  float* part;   // [tiles][4] partial sums of the four loss terms
+  float* part;   // [tiles][8 or 4] partial sums: L1 and SSIM of each workgroup, depth, normal
   float* loss;   // [5]
   int W, H, tiles_x, n_tiles;
   float fx, fy, cx, cy;
@@ -73,88 +92,90 @@ __device__ __forceinline__ float3 cross3(float3 a, float3 b) {
   return make_float3(fmaf(a.y, b.z, -a.z * b.y), fmaf(a.z, b.x, -a.x * b.z), fmaf(a.x, b.y, -a.y * b.x));
 }
 
-__global__ __launch_bounds__(kThreads) void maploss_fwd_kernel(Args a) {
-  __shared__ float sx[kS][kS], sy[kS][kS];
-  __shared__ double hs[5][kS][kT];
-  __shared__ float red[4][kThreads / 64];
-  const int t = threadIdx.x;
-  const int tx0 = (blockIdx.x % a.tiles_x) * kT, ty0 = (blockIdx.x / a.tiles_x) * kT;
-  const int HW = a.W * a.H;
-  const int ly = t / kT, lx = t - ly * kT;
-  const int gx = tx0 + lx, gy = ty0 + ly;
-  const bool inside = gx < a.W && gy < a.H;
-  const int p = gy * a.W + gx;
-  const float inv = 1.0f / (float)HW;
-  const double gs = -(double)a.w_ssim / (3.0 * (double)HW);  // dL/dSSIM_ch(p)
-  float l1 = 0.f, dssim = 0.f, ld = 0.f, ln = 0.f;
-  double ssum = 0.0;
-  // one colour channel at a time, so that the staging stays small enough for several
-  // workgroups per compute unit
-  for (int ch = 0; ch < 3; ++ch) {
-    if (ch) __syncthreads();
-    for (int k = t; k < kS * kS; k += kThreads) {
-      const int r = k / kS, c = k - r * kS;
-      const int yy = ty0 - kR + r, xx = tx0 - kR + c;
-      const bool in = xx >= 0 && xx < a.W && yy >= 0 && yy < a.H;
-      const int q = ch * HW + yy * a.W + xx;
-      sx[r][c] = in ? a.rgb[q] : 0.f;
-      sy[r][c] = in ? a.trgb[q] : 0.f;
-    }
-    __syncthreads();
-    // horizontal pass: x, y, x^2, y^2, xy along every staged row (FP64; the products of
-    // two floats are exact)
-    for (int k = t; k < kS * kT; k += kThreads) {
-      const int r = k / kT, c = k - r * kT;
-      double m0 = 0.0, m1 = 0.0, m2 = 0.0, m3 = 0.0, m4 = 0.0;
+__device__ __forceinline__ double wave_sum_d(double v) {
 #pragma unroll
-      for (int j = 0; j < 2 * kR + 1; ++j) {
-        const double x = sx[r][c + j], y = sy[r][c + j], g = a.win.gd[j];
-        m0 = fma(g, x, m0);
-        m1 = fma(g, y, m1);
-        m2 = fma(g, x * x, m2);
-        m3 = fma(g, y * y, m3);
-        m4 = fma(g, x * y, m4);
-      }
-      hs[0][r][c] = m0;
-      hs[1][r][c] = m1;
-      hs[2][r][c] = m2;
-      hs[3][r][c] = m3;
-      hs[4][r][c] = m4;
-    }
-    __syncthreads();
-    if (inside) {
-      // vertical pass, SSIM and its adjoint coefficients
-      double mx = 0.0, my = 0.0, exx = 0.0, eyy = 0.0, exy = 0.0;
+  for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+  return v;
+}
+
+// N planes' tiles with their halos (zero outside the image) to LDS, all loads issued
+// before the first store.
+template <int N>
+__device__ __forceinline__ void stage(float (&dst)[N][kSH][kSP], const float* const (&src)[N], int tx0, int ty0, int W,
+                                      int H, int t) {
+  constexpr int kN = (kSH * kSW + kThreads - 1) / kThreads;
+  float v[N][kN];
 #pragma unroll
-      for (int i = 0; i < 2 * kR + 1; ++i) {
-        const double g = a.win.gd[i];
-        mx = fma(g, hs[0][ly + i][lx], mx);
-        my = fma(g, hs[1][ly + i][lx], my);
-        exx = fma(g, hs[2][ly + i][lx], exx);
-        eyy = fma(g, hs[3][ly + i][lx], eyy);
-        exy = fma(g, hs[4][ly + i][lx], exy);
-      }
-      const double vx = fma(-mx, mx, exx), vy = fma(-my, my, eyy), cxy = fma(-mx, my, exy);
-      const double n1 = fma(2.0 * mx, my, kC1), n2 = fma(2.0, cxy, kC2);
-      const double d1 = fma(mx, mx, fma(my, my, kC1)), d2 = vx + vy + kC2;
-      const double rd = 1.0 / (d1 * d2);
-      const double s = n1 * n2 * rd;
-      ssum += s;
-      // ds/dmu_x (through mu_x, var_x and cov), ds/dE[x^2], ds/dE[xy]
-      const double ds_dm = fma(2.0 * my * (n2 - n1), rd, 2.0 * mx * s * (1.0 / d2 - 1.0 / d1));
-      const double ds_dxx = -s / d2;
-      const double ds_dxy = 2.0 * n1 * rd;
-      a.coef[(0 + ch) * HW + p] = (float)(gs * ds_dm);
-      a.coef[(3 + ch) * HW + p] = (float)(gs * ds_dxx);
-      a.coef[(6 + ch) * HW + p] = (float)(gs * ds_dxy);
-      l1 += fabsf(sx[ly + kR][lx + kR] - sy[ly + kR][lx + kR]);
-    }
+  for (int u = 0; u < kN; ++u) {
+    const int k = u * kThreads + t, r = k / kSW, c = k - r * kSW;
+    const int yy = ty0 - kR + r, xx = tx0 - kR + c;
+    const bool in = k < kSH * kSW && xx >= 0 && xx < W && yy >= 0 && yy < H;
+#pragma unroll
+    for (int m = 0; m < N; ++m) v[m][u] = in ? src[m][yy * W + xx] : 0.f;
   }
-  if (inside) {
-    dssim = (float)(1.0 - ssum * (1.0 / 3.0));
-    ld = fabsf(a.depth[p] - a.tdepth[p]);
+#pragma unroll
+  for (int u = 0; u < kN; ++u) {
+    const int k = u * kThreads + t, r = k / kSW, c = k - r * kSW;
+    if (k < kSH * kSW)
+#pragma unroll
+      for (int m = 0; m < N; ++m) dst[m][r][c] = v[m][u];
+  }
+}
+
+// The tile and the part (channel, or last the depth) of a workgroup.  Workgroups are dealt
+// round-robin to the 8 XCDs, each with an L2 of its own: XCD k takes the k-th eighth of
+// the tiles, so that the halos and the 128-byte lines that neighbouring tiles share are
+// fetched, and merged when written, once.
+__device__ __forceinline__ void tile_of(int n_tiles, int& tile, int& part) {
+  const int per = (n_tiles + kXcds - 1) / kXcds;
+  const int j = (int)blockIdx.x / kXcds;
+  part = j / per;
+  tile = (int)blockIdx.x % kXcds * per + (j - part * per);
+}
+
+// The kRun + kTaps - 1 staged values of a run (src 16-byte aligned).
+__device__ __forceinline__ void load_run(const float* src, float (&v)[kRun + kTaps - 1]) {
+  static_assert(kRun + kTaps - 1 == 14, "run");
+  const float4 a = *reinterpret_cast<const float4*>(src), b = *reinterpret_cast<const float4*>(src + 4);
+  const float4 c = *reinterpret_cast<const float4*>(src + 8);
+  const float2 d = *reinterpret_cast<const float2*>(src + 12);
+  v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+  v[8] = c.x, v[9] = c.y, v[10] = c.z, v[11] = c.w, v[12] = d.x, v[13] = d.y;
+}
+
+// The workgroup's sums of two loss terms to out[0], out[1].
+__device__ __forceinline__ void store_terms(double v0, double v1, int t, float* out) {
+  __shared__ double red[2][kThreads / 64];
+  v0 = wave_sum_d(v0);
+  v1 = wave_sum_d(v1);
+  if ((t & 63) == 0) {
+    red[0][t >> 6] = v0;
+    red[1][t >> 6] = v1;
+  }
+  __syncthreads();
+  if (t < 2) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) s += red[t][w];
+    out[t] = (float)s;
+  }
+}
+
+// The depth and normal terms of one tile.
+__device__ __forceinline__ void fwd_depth(const Args& a, int tx0, int ty0, int t, float* out) {
+  const int HW = a.W * a.H;
+  const float inv = 1.0f / (float)HW;
+  const int gx = tx0 + t % kTW;
+  float ld = 0.f, ln = 0.f;
+#pragma unroll
+  for (int o = 0; o < kRows; ++o) {
+    const int gy = ty0 + o * (kThreads / kTW) + t / kTW;
+    if (gx >= a.W || gy >= a.H) continue;
+    const int p = gy * a.W + gx;
+    ld += fabsf(a.depth[p] - a.tdepth[p]);
     // depth normal from the central differences of the back-projected neighbours,
     // in the cancellation-free form D(x+1)(x+1-cx) - D(x-1)(x-1-cx) = dD (x-cx) + sD
+    const float N0 = a.normal[p], N1 = a.normal[HW + p], N2 = a.normal[2 * HW + p];
     float3 nd = make_float3(0.f, 0.f, 0.f), gdx = nd, gdy = nd;
     if (gx >= 1 && gx <= a.W - 2 && gy >= 1 && gy <= a.H - 2) {
       const float xh = ((float)gx - a.cx) / a.fx, yh = ((float)gy - a.cy) / a.fy;
@@ -167,7 +188,6 @@ __global__ __launch_bounds__(kThreads) void maploss_fwd_kernel(Args a) {
       if (c2 > 0.f) {
         const float nc = sqrtf(c2), rn = 1.0f / nc;
         nd = make_float3(c.x * rn, c.y * rn, c.z * rn);
-        const float N0 = a.normal[p], N1 = a.normal[HW + p], N2 = a.normal[2 * HW + p];
         const float dot = fmaf(nd.x, N0, fmaf(nd.y, N1, nd.z * N2));
         // dL/dc = -w_n/HW (N - (N_D . N) N_D) / |c|
         const float k = -a.w_n * inv * rn;
@@ -176,8 +196,7 @@ __global__ __launch_bounds__(kThreads) void maploss_fwd_kernel(Args a) {
         gdy = cross3(G, vx);  // dL/d(dy) = G x dx
       }
     }
-    const float N0 = a.normal[p], N1 = a.normal[HW + p], N2 = a.normal[2 * HW + p];
-    ln = 1.0f - fmaf(nd.x, N0, fmaf(nd.y, N1, nd.z * N2));
+    ln += 1.0f - fmaf(nd.x, N0, fmaf(nd.y, N1, nd.z * N2));
     const float kn = -a.w_n * inv;
     a.d_normal[p] = kn * nd.x;
     a.d_normal[HW + p] = kn * nd.y;
@@ -189,100 +208,223 @@ __global__ __launch_bounds__(kThreads) void maploss_fwd_kernel(Args a) {
     a.gdiff[4 * HW + p] = gdy.y;
     a.gdiff[5 * HW + p] = gdy.z;
   }
-  const float v[4] = {wave_sum(l1), wave_sum(dssim), wave_sum(ld), wave_sum(ln)};
-  if ((t & 63) == 0)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) red[q][t >> 6] = v[q];
-  __syncthreads();
-  if (t < 4) {
-    float s = 0.f;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) s += red[t][w];
-    a.part[blockIdx.x * 4 + t] = s;
-  }
+  store_terms(ld, ln, t, out);
 }
 
-__global__ __launch_bounds__(kThreads) void maploss_bwd_kernel(Args a) {
-  __shared__ float sc[3][kS][kS];
-  __shared__ float hc[3][kS][kT];
-  __shared__ float red[4][kThreads / 64];
+template <int CH>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void maploss_fwd_kernel(Args a) {
+  // the staged planes, then (once every thread has read its runs) the horizontal sums
+  __shared__ union {
+    float in[2][kSH][kSP];
+    double hs[kStats][kSH][kTW];
+  } sh;
   const int t = threadIdx.x;
-  const int tx0 = (blockIdx.x % a.tiles_x) * kT, ty0 = (blockIdx.x / a.tiles_x) * kT;
+  int tile, y;
+  tile_of(a.n_tiles, tile, y);
+  if (tile >= a.n_tiles) return;
+  const int tx0 = (tile % a.tiles_x) * kTW, ty0 = (tile / a.tiles_x) * kTH;
+  float* const part = a.part + (size_t)tile * (CH == 1 ? 8 : 4) + 2 * y;
+  if (y * CH == 3) {
+    fwd_depth(a, tx0, ty0, t, part);
+    return;
+  }
   const int HW = a.W * a.H;
-  const int ly = t / kT, lx = t - ly * kT;
-  const int gx = tx0 + lx, gy = ty0 + ly;
-  const bool inside = gx < a.W && gy < a.H;
-  const int p = gy * a.W + gx;
-  const float inv = 1.0f / (float)HW;
-  // one colour channel at a time: its A, B, C planes filtered, then its d_rgb
-  for (int ch = 0; ch < 3; ++ch) {
-    if (ch) __syncthreads();
-    for (int k = t; k < kS * kS; k += kThreads) {
-      const int r = k / kS, c = k - r * kS;
-      const int yy = ty0 - kR + r, xx = tx0 - kR + c;
-      const bool in = xx >= 0 && xx < a.W && yy >= 0 && yy < a.H;
-      const int q = yy * a.W + xx;
-#pragma unroll
-      for (int m = 0; m < 3; ++m) sc[m][r][c] = in ? a.coef[(3 * m + ch) * HW + q] : 0.f;
-    }
+  const int lx = t % kTW, ly0 = t / kTW * kRows;
+  const int gx = tx0 + lx;
+  const double gs = -(double)a.w_ssim / (3.0 * (double)HW);  // dL/dSSIM_ch(p)
+  float l1 = 0.f;
+  double dssim = 0.0;
+  const int ch0 = y * CH;
+  for (int ch = ch0; ch < ch0 + CH; ++ch) {
+    if (ch > ch0) __syncthreads();
+    stage<2>(sh.in, {a.rgb + (size_t)ch * HW, a.trgb + (size_t)ch * HW}, tx0, ty0, a.W, a.H, t);
     __syncthreads();
-    for (int k = t; k < 3 * kS * kT; k += kThreads) {
-      const int m = k / (kS * kT), rem = k - m * (kS * kT), r = rem / kT, c = rem - r * kT;
-      float acc = 0.f;
+    // horizontal pass along every staged row (FP64; the products of two floats are exact)
+    const int r = t / kRuns, c0 = t % kRuns * kRun;
+    double m[kRun][kStats] = {};
+    if (t < kSH * kRuns) {
+      float xr[kRun + kTaps - 1], yr[kRun + kTaps - 1];
+      load_run(&sh.in[0][r][c0], xr);
+      load_run(&sh.in[1][r][c0], yr);
+      if (r >= kR && r < kR + kTH && ty0 + r - kR < a.H)
 #pragma unroll
-      for (int j = 0; j < 2 * kR + 1; ++j) acc = fmaf(a.win.g[j], sc[m][r][c + j], acc);
-      hc[m][r][c] = acc;
-    }
-    __syncthreads();
-    if (inside) {
-      float f[3];
+        for (int o = 0; o < kRun; ++o) l1 += tx0 + c0 + o < a.W ? fabsf(xr[o + kR] - yr[o + kR]) : 0.f;
 #pragma unroll
-      for (int m = 0; m < 3; ++m) {
-        float acc = 0.f;
+      for (int i = 0; i < kRun + kTaps - 1; ++i) {
+        const double x = xr[i], y = yr[i];
+        const double ss = fma(y, y, x * x), xy = x * y;
 #pragma unroll
-        for (int i = 0; i < 2 * kR + 1; ++i) acc = fmaf(a.win.g[i], hc[m][ly + i][lx], acc);
-        f[m] = acc;
+        for (int o = 0; o < kRun; ++o) {
+          if (i - o < 0 || i - o >= kTaps) continue;
+          const double g = a.win.gd[i - o];
+          m[o][0] = fma(g, x, m[o][0]);
+          m[o][1] = fma(g, y, m[o][1]);
+          m[o][2] = fma(g, ss, m[o][2]);
+          m[o][3] = fma(g, xy, m[o][3]);
+        }
       }
-      const float x = a.rgb[ch * HW + p], y = a.trgb[ch * HW + p];
-      a.d_rgb[ch * HW + p] = fmaf(a.w_l1 * inv, sgn(x - y), fmaf(2.f * x, f[1], fmaf(y, f[2], f[0])));
+    }
+    __syncthreads();
+    if (t < kSH * kRuns)
+#pragma unroll
+      for (int q = 0; q < kStats; ++q)
+#pragma unroll
+        for (int o = 0; o < kRun; ++o) sh.hs[q][r][c0 + o] = m[o][q];
+    __syncthreads();
+    // vertical pass, SSIM and its adjoint coefficients
+    double v[kRows][kStats] = {};
+#pragma unroll
+    for (int i = 0; i < kRows + kTaps - 1; ++i) {
+#pragma unroll
+      for (int q = 0; q < kStats; ++q) {
+        const double h = sh.hs[q][ly0 + i][lx];
+#pragma unroll
+        for (int o = 0; o < kRows; ++o)
+          if (i - o >= 0 && i - o < kTaps) v[o][q] = fma(a.win.gd[i - o], h, v[o][q]);
+      }
+    }
+    // (computed here: moved into the branches below, the sums would keep every h alive)
+#pragma unroll
+    for (int o = 0; o < kRows; ++o)
+#pragma unroll
+      for (int q = 0; q < kStats; ++q) asm volatile("" : "+v"(v[o][q]));
+#pragma unroll
+    for (int o = 0; o < kRows; ++o) {
+      const int gy = ty0 + ly0 + o;
+      if (gx >= a.W || gy >= a.H) continue;
+      const int p = gy * a.W + gx;
+      const double mx = v[o][0], my = v[o][1], cxy = fma(-mx, my, v[o][3]);
+      const double var = fma(-mx, mx, fma(-my, my, v[o][2]));  // of x plus of y
+      const double n1 = fma(2.0 * mx, my, kC1), n2 = fma(2.0, cxy, kC2);
+      const double d1 = fma(mx, mx, fma(my, my, kC1)), d2 = var + kC2;
+      const double rd = 1.0 / (d1 * d2), r1 = rd * d2, r2 = rd * d1;  // 1 / d1, 1 / d2
+      const double s = n1 * n2 * rd;
+      dssim += (1.0 - s) * (1.0 / 3.0);
+      // ds/dmu_x (through mu_x, var_x and cov), ds/dE[x^2], ds/dE[xy]
+      const double ds_dm = fma(2.0 * my * (n2 - n1), rd, 2.0 * mx * s * (r2 - r1));
+      const double ds_dxx = -s * r2;
+      const double ds_dxy = 2.0 * n1 * rd;
+      a.coef[(0 + ch) * HW + p] = (float)(gs * ds_dm);
+      a.coef[(3 + ch) * HW + p] = (float)(gs * ds_dxx);
+      a.coef[(6 + ch) * HW + p] = (float)(gs * ds_dxy);
     }
   }
-  if (inside) {
-    // d_depth: the depth L1 term, and the gradients of the neighbour differences that
-    // contain this pixel: +dx of the left neighbour, -dx of the right one, +dy of the one
-    // above, -dy of the one below (zero outside the image)
+  store_terms(l1, dssim, t, part);
+}
+
+// d_depth of one tile: the depth L1 term, and the gradients of the neighbour differences
+// that contain the pixel: +dx of the left neighbour, -dx of the right one, +dy of the one
+// above, -dy of the one below (zero outside the image).
+__device__ __forceinline__ void bwd_depth(const Args& a, int tx0, int ty0, int t) {
+  const int HW = a.W * a.H;
+  const float inv = 1.0f / (float)HW;
+  const int gx = tx0 + t % kTW;
+#pragma unroll
+  for (int o = 0; o < kRows; ++o) {
+    const int gy = ty0 + o * (kThreads / kTW) + t / kTW;
+    if (gx >= a.W || gy >= a.H) continue;
+    const int p = gy * a.W + gx;
     float3 acc = make_float3(0.f, 0.f, 0.f);
     if (gx >= 1) {
-      const int o = p - 1;
-      acc.x += a.gdiff[o], acc.y += a.gdiff[HW + o], acc.z += a.gdiff[2 * HW + o];
+      const int n = p - 1;
+      acc.x += a.gdiff[n], acc.y += a.gdiff[HW + n], acc.z += a.gdiff[2 * HW + n];
     }
     if (gx <= a.W - 2) {
-      const int o = p + 1;
-      acc.x -= a.gdiff[o], acc.y -= a.gdiff[HW + o], acc.z -= a.gdiff[2 * HW + o];
+      const int n = p + 1;
+      acc.x -= a.gdiff[n], acc.y -= a.gdiff[HW + n], acc.z -= a.gdiff[2 * HW + n];
     }
     if (gy >= 1) {
-      const int o = p - a.W;
-      acc.x += a.gdiff[3 * HW + o], acc.y += a.gdiff[4 * HW + o], acc.z += a.gdiff[5 * HW + o];
+      const int n = p - a.W;
+      acc.x += a.gdiff[3 * HW + n], acc.y += a.gdiff[4 * HW + n], acc.z += a.gdiff[5 * HW + n];
     }
     if (gy <= a.H - 2) {
-      const int o = p + a.W;
-      acc.x -= a.gdiff[3 * HW + o], acc.y -= a.gdiff[4 * HW + o], acc.z -= a.gdiff[5 * HW + o];
+      const int n = p + a.W;
+      acc.x -= a.gdiff[3 * HW + n], acc.y -= a.gdiff[4 * HW + n], acc.z -= a.gdiff[5 * HW + n];
     }
     const float xh = ((float)gx - a.cx) / a.fx, yh = ((float)gy - a.cy) / a.fy;
     const float dr = fmaf(acc.x, xh, fmaf(acc.y, yh, acc.z));
     a.d_depth[p] = fmaf(a.w_d * inv, sgn(a.depth[p] - a.tdepth[p]), dr);
   }
+}
+
+template <int CH>
+__global__ __launch_bounds__(kThreads) void maploss_bwd_kernel(Args a) {
+  __shared__ __align__(16) float sc[3][kSH][kSP];
+  __shared__ __align__(16) float hc[3][kSH][kTW];
+  __shared__ double red[4];
+  const int t = threadIdx.x;
+  int tile, y;
+  tile_of(a.n_tiles, tile, y);
+  if (tile >= a.n_tiles) return;
+  const int tx0 = (tile % a.tiles_x) * kTW, ty0 = (tile / a.tiles_x) * kTH;
+  if (y * CH == 3) {
+    bwd_depth(a, tx0, ty0, t);
+    return;
+  }
+  const int HW = a.W * a.H;
+  const int lx = t % kTW, ly0 = t / kTW * kRows;
+  const int gx = tx0 + lx;
+  const float inv = 1.0f / (float)HW;
+  const int ch0 = y * CH;
+  // a colour channel's A, B, C planes filtered, then its d_rgb
+  for (int ch = ch0; ch < ch0 + CH; ++ch) {
+    if (ch > ch0) __syncthreads();
+    float xo[kRows], yo[kRows];
+#pragma unroll
+    for (int o = 0; o < kRows; ++o) {
+      const int gy = ty0 + ly0 + o;
+      const bool in = gx < a.W && gy < a.H;
+      xo[o] = in ? a.rgb[ch * HW + gy * a.W + gx] : 0.f;
+      yo[o] = in ? a.trgb[ch * HW + gy * a.W + gx] : 0.f;
+    }
+    const float* const c = a.coef + (size_t)ch * HW;
+    stage<3>(sc, {c, c + (size_t)3 * HW, c + (size_t)6 * HW}, tx0, ty0, a.W, a.H, t);
+    __syncthreads();
+    for (int k = t; k < 3 * kSH * kRuns; k += kThreads) {
+      const int r = k / kRuns, c0 = k % kRuns * kRun;  // (row r of the three planes' rows)
+      float in[kRun + kTaps - 1], f[kRun] = {};
+      load_run(&sc[0][0][0] + r * kSP + c0, in);
+#pragma unroll
+      for (int o = 0; o < kRun; ++o)
+#pragma unroll
+        for (int j = 0; j < kTaps; ++j) f[o] = fmaf(a.win.g[j], in[o + j], f[o]);
+      *reinterpret_cast<float4*>(&hc[0][0][0] + r * kTW + c0) = make_float4(f[0], f[1], f[2], f[3]);
+    }
+    __syncthreads();
+    float f[kRows][3] = {};
+#pragma unroll
+    for (int i = 0; i < kRows + kTaps - 1; ++i) {
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        const float h = hc[m][ly0 + i][lx];
+#pragma unroll
+        for (int o = 0; o < kRows; ++o)
+          if (i - o >= 0 && i - o < kTaps) f[o][m] = fmaf(a.win.g[i - o], h, f[o][m]);
+      }
+    }
+#pragma unroll
+    for (int o = 0; o < kRows; ++o) {
+      const int gy = ty0 + ly0 + o;
+      if (gx >= a.W || gy >= a.H) continue;
+      a.d_rgb[ch * HW + gy * a.W + gx] =
+          fmaf(a.w_l1 * inv, sgn(xo[o] - yo[o]), fmaf(2.f * xo[o], f[o][1], fmaf(yo[o], f[o][2], f[o][0])));
+    }
+  }
   if (blockIdx.x == 0) {
     // the loss: wave q adds term q's partials in a fixed order
     const int wave = t >> 6, lane = t & 63;
-    float s = 0.f;
-    for (int b = lane; b < a.n_tiles; b += 64) s += a.part[b * 4 + wave];
-    s = wave_sum(s);
-    if (lane == 0) red[wave][0] = s;
+    double s = 0.0;
+    for (int b = lane; b < a.n_tiles; b += 64) {
+      if (CH == 3) s += a.part[b * 4 + wave];
+      else if (wave >= 2) s += a.part[b * 8 + 4 + wave];
+      else s += (double)a.part[b * 8 + wave] + (double)a.part[b * 8 + 2 + wave] + (double)a.part[b * 8 + 4 + wave];
+    }
+    s = wave_sum_d(s);
+    if (lane == 0) red[wave] = s;
     __syncthreads();
     if (t == 0) {
-      const float inv = 1.0f / (float)HW;
-      const float m1 = red[0][0] * inv, m2 = red[1][0] * inv, m3 = red[2][0] * inv, m4 = red[3][0] * inv;
+      const float m1 = (float)(red[0] / HW), m2 = (float)(red[1] / HW), m3 = (float)(red[2] / HW),
+                  m4 = (float)(red[3] / HW);
       a.loss[1] = m1;
       a.loss[2] = m2;
       a.loss[3] = m3;
@@ -311,7 +453,8 @@ using namespace gs2d::maploss;
 
 GS2D_API int64_t gs2d_mapping_loss_workspace(int32_t width, int32_t height) {
   if (width <= 0 || height <= 0) return 0;
-  const int64_t tiles = (int64_t)((width + kT - 1) / kT) * ((height + kT - 1) / kT);
+  // 15 planes, and the partial sums (four per 16 x 16 pixels; a tile needs up to eight)
+  const int64_t tiles = (int64_t)((width + 15) / 16) * ((height + 15) / 16);
   return 15 * (int64_t)width * height + 4 * tiles;
 }
 
@@ -339,8 +482,8 @@ GS2D_API int gs2d_mapping_loss(const gs2d_camera* camera, const float* rgb, cons
   a.gdiff = work + 9 * HW;
   a.part = work + 15 * HW;
   a.loss = loss;
-  a.tiles_x = (a.W + kT - 1) / kT;
-  a.n_tiles = a.tiles_x * ((a.H + kT - 1) / kT);
+  a.tiles_x = (a.W + kTW - 1) / kTW;
+  a.n_tiles = a.tiles_x * ((a.H + kTH - 1) / kTH);
   a.fx = camera->fx;
   a.fy = camera->fy;
   a.cx = camera->cx;
@@ -351,7 +494,15 @@ GS2D_API int gs2d_mapping_loss(const gs2d_camera* camera, const float* rgb, cons
   a.w_d = w.w_d;
   a.w_n = w.w_n;
   a.win = make_window();
-  maploss_fwd_kernel<<<a.n_tiles, kThreads, 0, stream>>>(a);
-  maploss_bwd_kernel<<<a.n_tiles, kThreads, 0, stream>>>(a);
+  // one channel per workgroup, with eight partials per tile; images of up to 16 rows, whose
+  // workspace has room for four, take the three channels in one
+  const int padded = (a.n_tiles + kXcds - 1) / kXcds * kXcds;
+  if (a.H > 16) {
+    maploss_fwd_kernel<1><<<4 * padded, kThreads, 0, stream>>>(a);
+    maploss_bwd_kernel<1><<<4 * padded, kThreads, 0, stream>>>(a);
+  } else {
+    maploss_fwd_kernel<3><<<2 * padded, kThreads, 0, stream>>>(a);
+    maploss_bwd_kernel<3><<<2 * padded, kThreads, 0, stream>>>(a);
+  }
   return hipGetLastError() == hipSuccess ? GS2D_OK : GS2D_ERR_HIP;
 }
