@@ -1,8 +1,8 @@
 #!/usr/bin/env python3
-"""Benchmark: graph-captured 2DGS tracking iterations at 640x480 with 300k surfels on one MI355X.
+"""Benchmark: 2DGS tracking iterations at 640x480 with 300k surfels on one MI355X.
 
 One step is one tracking iteration of the whole hot path: per-surfel preprocessing,
-the pair duplication, the tile sort with the tile ranges, and the tracking walk (each
+the pair duplication, the tile ranges and the placement by tile, and the tracking walk (each
 tile's list put in depth order, then the forward blend of colour/depth/normal/
 opacity, the tracking loss with its masks and the pose-only backward with the se(3)
 pose reduction in one walk), and the AdamW + Exp pose step.  Inputs (a seeded synthetic 6x5x3 m room with 20 boxes, 300,000 surfels,
@@ -464,7 +464,7 @@ def config3_bench(args):
 
 def config4_bench(args):
     """Batched tracking: 32 independent problems (320x240 .. 1200x680, 50k .. 1M surfels,
-    2-8 cm / 1-5 deg starts), 50 graph-captured iterations of all 32 in one launch per
+    2-8 cm / 1-5 deg starts), 50 iterations of all 32 in one launch per
     kernel per iteration; aggregate iterations/s and per-problem convergence."""
     import numpy as np
     import torch
@@ -698,7 +698,7 @@ def main():
                           for k in range(1, args.held_out_rooms + 1))]
         del rw, net
 
-    # warm-up and timed graph replays
+    # warm-up and timed iterations
     log("warm-up")
     pose.copy_(start_dev)
     r.track(P, cam, pose, tgt_rgb, tgt_depth, n_iters=args.warmup, lr=LR, use_graph=True, history=False)
@@ -714,7 +714,7 @@ def main():
 
     # eager passes of the same loop: one counting the blend work units (the counting
     # kernels are slower), one timing each kernel family with HIP events on the launch
-    # stream while running the same kernels as the graph
+    # stream while running the same kernels
     log("profiled eager passes")
     pose.copy_(start_dev)
     torch.cuda.synchronize()

@@ -190,7 +190,7 @@ typedef struct gs2d_track_args {
   int32_t n_iters;
   float lr[6];               /* per-component learning rates (rho then phi) */
   float beta1, beta2, eps, weight_decay;
-  int32_t use_graph;         /* 1: capture one iteration into a HIP graph and replay it */
+  int32_t use_graph;         /* 1: run on a stream of the context, its buffers kept sized */
   float* pose_history;       /* [n_iters][12] pose after each step, or NULL */
   float* loss_history;       /* [n_iters] loss before each step, or NULL */
   double* grad_history;      /* [n_iters][6] pose gradient (rho, phi) each step consumed, FP64
@@ -351,9 +351,8 @@ GS2D_API int gs2d_tracking_error(gs2d_ctx* ctx, const gs2d_camera* camera, const
 /* Run the tracking loop described at gs2d_track_args (the pose update of Sec.
  * "Tracking and Keyframe Selection": AdamW on the pose, surfels frozen).  The
  * first call sizes the pair buffers on the start pose (one synchronising render).
- * With use_graph the iteration is captured once on a stream of the context and
- * replayed; the instantiated graph is kept and reused by later calls with the same
- * buffers and hyper-parameters.  Returns after the work has completed (the call
+ * With use_graph the loop runs on a stream of the context, and later calls with the same
+ * buffers and hyper-parameters skip that sizing.  Returns after the work has completed (the call
  * synchronises).  On a pair overflow the loop restarts from the start pose with
  * larger buffers (up to 3 attempts, then GS2D_ERR_CAPACITY).  GS2D_ERR_NONFINITE
  * when a surfel or the pose held a value that is not finite (such surfels are culled
@@ -368,7 +367,7 @@ GS2D_API int gs2d_track(gs2d_ctx* ctx, const gs2d_track_args* args, hipStream_t 
  * constants and use_graph (its params/n/camera/pose/target fields are ignored);
  * its pose_history is [n_iters][n_problems][12], loss_history [n_iters][n_problems] and
  * grad_history [n_iters][n_problems][6].
- * Same graph caching, synchronisation and restart rules as gs2d_track. */
+ * Same sizing, synchronisation and restart rules as gs2d_track. */
 GS2D_API int gs2d_track_batch(gs2d_ctx* ctx, const gs2d_track_problem* problems, int32_t n_problems,
                               const gs2d_track_args* common, hipStream_t stream);
 

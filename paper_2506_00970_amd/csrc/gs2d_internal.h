@@ -80,7 +80,7 @@ struct Ctrl {            // device-resident counters and tracking state
   int32_t max_hist;
   int32_t n_views;
   unsigned long long work[4];  // profile counters: fwd evaluated, fwd covering, bwd evaluated, bwd covering
-  uint32_t iter_v[kMaxViews];  // tracking iteration of each view (graph replays)
+  uint32_t iter_v[kMaxViews];  // tracking iteration of each view
   double loss[kMaxViews];
   double adam_m[kMaxViews][6];
   double adam_v[kMaxViews][6];
@@ -196,17 +196,16 @@ struct gs2d_ctx {
   // pair total to: the render waits for it without a copy (np_dev: its device address)
   volatile uint32_t* np_host = nullptr;
   uint32_t* np_dev = nullptr;
-  hipStream_t graph_stream = nullptr;  // capture stream of the tracking loop (default priority)
+  hipStream_t graph_stream = nullptr;  // the tracking loop's own stream (default priority)
 
-  // cached tracking graph (invalidated whenever a workspace buffer moves)
-  hipGraphExec_t track_exec = nullptr;
-  hipGraph_t track_graph = nullptr;
+  // what the last tracking call with use_graph was sized for (until a workspace buffer moves)
   std::vector<unsigned char> track_key;
   bool track_valid = false;
 
   // profiling: HIP events around kernel families (eager calls only)
   struct EvPair { hipEvent_t a, b; int fam; };
   EvPair* ev = nullptr;
+  bool prof_off = false;       // in a tracking loop on the context's stream
   int ev_used = 0, ev_cap = 0;
   double prof_ms[gs2d::kNumFamilies] = {0};
   long long prof_launches[gs2d::kNumFamilies] = {0};
