@@ -331,16 +331,48 @@ int render_views(gs2d_ctx* ctx, const ViewSet& vs, hipStream_t s, bool allow_syn
       ProfScope ps(ctx, kScan, s);
       launch_part_scan(part_pairs, part_vis, items, ctx->ctrl, np_out, s);
     }
-    auto duplicate = [&](uint32_t* np_dst) {
-      ProfScope ps(ctx, kDup, s);
-      launch_duplicate(ctx->count, part_pairs, part_vis, scanned, ctx->rect, ctx->views, nv, items, ctx->p_cap,
-                       ctx->dkey, ctx->pairs, ctx->tcount, (int)vs.tiles, ctx->ctrl, np_dst, s);
+    // many more tiles than fit on the GPU at once: the blends take the longest lists first
+    ctx->order_on = blend && vs.tiles > kOrderMinTiles;
+    auto pairs_and_blend = [&](uint32_t* np_dst) {
+      {
+        ProfScope ps(ctx, kDup, s);
+        launch_duplicate(ctx->count, part_pairs, part_vis, scanned, ctx->rect, ctx->views, nv, items, ctx->p_cap,
+                         ctx->dkey, ctx->pairs, ctx->tcount, (int)vs.tiles, ctx->ctrl, np_dst, s);
+      }
+      if (ctx->opt.keep_unsorted && ctx->pkey_keep)
+        launch_split_pairs(ctx->pairs, ctx->p_cap, ctx->pkey_keep, ctx->pval_keep, s);
+      {
+        ProfScope ps(ctx, kRanges, s);
+        launch_ranges(ctx->tcount, (int)vs.tiles, ctx->ctrl, ctx->ranges, ctx->order_on ? ctx->order : nullptr, s);
+      }
+      {
+        ProfScope ps(ctx, kTileSort, s);
+        launch_place(ctx->pairs, ctx->ctrl, ctx->p_cap, ctx->ranges, (int)vs.tiles, ctx->placed, s);
+      }
+      if (order) {
+        // each tile's pairs into depth order
+        ProfScope ps(ctx, kDepthSort, s);
+        launch_tile_order(ctx->ranges, (int)vs.tiles, ctx->placed, reinterpret_cast<uint64_t*>(ctx->pairs), ctx->ids,
+                          s);
+      }
+      if (!blend) return;
+      BlendArgs ba = blend_args(ctx, vs);
+      if (ro) {
+        ba.res_x = ro->x;
+        ba.res_part = ro->part;
+        ba.lambda_d = ro->lambda_d;
+      }
+      // (the outputs are zero: preprocessing)
+      for (int k = 0; k < nv; ++k) ba.contrib = ba.contrib || vs.v[k].contrib != nullptr;
+      ProfScope ps(ctx, kBlendFwd, s);
+      launch_blend_fwd(ba, tw, th, ctx->t_final, ctx->last, work_ptr(ctx, s), s);
     };
-    duplicate(np_out);
+    pairs_and_blend(np_out);
     if (read_np) {
       // the total is written early (by the scan, or by the duplication's first
-      // workgroup): wait for the word itself rather than the whole stream, so that the
-      // launches below are queued before the duplication ends
+      // workgroup): wait for the word itself rather than the whole stream.  Everything is
+      // launched before the wait, so that the GPU does not wait for the host in turn; when
+      // the pairs did not fit, the lists are empty and the launches so far cost little
       uint32_t np32 = *ctx->np_host;
       while (np32 == kNpPending) {
         const hipError_t q = hipStreamQuery(s);
@@ -355,45 +387,11 @@ int render_views(gs2d_ctx* ctx, const ViewSet& vs, hipStream_t s, bool allow_syn
       ctx->host_ctrl->n_pairs = np32;  // for callers that size buffers from this render
       if (np > ctx->p_cap) {
         GS2D_HIP(ctx, hipStreamSynchronize(s));
-        // grow and duplicate again (the first pass counted part of its pairs)
-        ctx->tcount_fresh = true;
+        // grow and go through the pairs again
         GS2D_TRY(ensure_pairs(ctx, np + np / 4));
-        clear_fresh_counts(ctx, s);
         launch_fill_u32(&ctx->ctrl->overflow, 0u, 1, s);  // set by the first pass
-        duplicate(nullptr);
+        pairs_and_blend(nullptr);
       }
-    }
-    if (ctx->opt.keep_unsorted && ctx->pkey_keep)
-      launch_split_pairs(ctx->pairs, ctx->p_cap, ctx->pkey_keep, ctx->pval_keep, s);
-    // many more tiles than fit on the GPU at once: the blends take the longest lists first
-    ctx->order_on = blend && vs.tiles > kOrderMinTiles;
-    {
-      ProfScope ps(ctx, kRanges, s);
-      launch_ranges(ctx->tcount, (int)vs.tiles, ctx->ctrl, ctx->ranges, ctx->order_on ? ctx->order : nullptr, s);
-    }
-    {
-      ProfScope ps(ctx, kTileSort, s);
-      launch_place(ctx->pairs, ctx->ctrl, ctx->p_cap, ctx->ranges, (int)vs.tiles, ctx->placed, s);
-    }
-    if (order) {
-      // each tile's pairs into depth order
-      ProfScope ps(ctx, kDepthSort, s);
-      launch_tile_order(ctx->ranges, (int)vs.tiles, ctx->placed, reinterpret_cast<uint64_t*>(ctx->pairs), ctx->ids, s);
-    }
-    BlendArgs ba = blend_args(ctx, vs);
-    if (ro) {
-      ba.res_x = ro->x;
-      ba.res_part = ro->part;
-      ba.lambda_d = ro->lambda_d;
-    }
-    if (blend) {
-      for (int k = 0; k < nv; ++k)
-        if (vs.v[k].contrib) {
-          launch_fill_f32(vs.v[k].contrib, 0.f, vs.v[k].n, s);
-          ba.contrib = true;
-        }
-      ProfScope ps(ctx, kBlendFwd, s);
-      launch_blend_fwd(ba, tw, th, ctx->t_final, ctx->last, work_ptr(ctx, s), s);
     }
   }
   GS2D_HIP(ctx, hipGetLastError());

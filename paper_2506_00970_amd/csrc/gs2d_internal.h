@@ -229,8 +229,8 @@ namespace gs2d {
 void launch_upload_views(const ViewSet& vs, ViewDesc* dst, hipStream_t s, Ctrl* ctrl = nullptr);
 constexpr int kPartItems = 256;  // items per preprocessing block (per-block pair counts)
 // Per item: record, tile rectangle, tile count and depth key (0xFFFFFFFF for items
-// that touch no tile); per block of kPartItems items: the pair count and the count of
-// items that touch a tile.  clear_overflow: clears ctrl->overflow (a tracking loop
+// that touch no tile), zero contribution; per block of kPartItems items: the pair count
+// and the count of items that touch a tile.  clear_overflow: clears ctrl->overflow (a tracking loop
 // keeps it from the start of the call, so that an overflow in any iteration is seen).
 void launch_preprocess(const ViewDesc* views, int n_views, int64_t items, float z_near, int filter, int tile_w,
                        int tile_h, float4* rec, uint2* rect, uint32_t* count, uint32_t* dkey, float* saved_pose,

@@ -54,6 +54,7 @@ __device__ inline uint32_t preprocess_item(const ViewDesc* __restrict__ views, i
   // has fewer than 12)
   if (saved_pose)
     for (int j = i; j < 12; j += n) saved_pose[v * 12 + j] = pose[j];
+  if (V.contrib) V.contrib[i] = 0.f;  // (the forward blend adds to it)
   double R[9], t[3];
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
