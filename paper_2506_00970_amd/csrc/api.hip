@@ -342,18 +342,15 @@ int render_views(gs2d_ctx* ctx, const ViewSet& vs, hipStream_t s, bool allow_syn
       if (ctx->opt.keep_unsorted && ctx->pkey_keep)
         launch_split_pairs(ctx->pairs, ctx->p_cap, ctx->pkey_keep, ctx->pval_keep, s);
       {
-        ProfScope ps(ctx, kRanges, s);
-        launch_ranges(ctx->tcount, (int)vs.tiles, ctx->ctrl, ctx->ranges, ctx->order_on ? ctx->order : nullptr, s);
-      }
-      {
         ProfScope ps(ctx, kTileSort, s);
-        launch_place(ctx->pairs, ctx->ctrl, ctx->p_cap, ctx->ranges, (int)vs.tiles, ctx->placed, s);
+        launch_ranges_place(ctx->tcount, (int)vs.tiles, ctx->pairs, ctx->ctrl, ctx->p_cap, ctx->ranges,
+                            ctx->order_on ? ctx->order : nullptr, ctx->placed, s);
       }
       if (order) {
         // each tile's pairs into depth order
         ProfScope ps(ctx, kDepthSort, s);
         launch_tile_order(ctx->ranges, (int)vs.tiles, ctx->placed, reinterpret_cast<uint64_t*>(ctx->pairs), ctx->ids,
-                          s);
+                          ctx->tcount, s);
       }
       if (!blend) return;
       BlendArgs ba = blend_args(ctx, vs);
@@ -607,6 +604,7 @@ int track_iteration(gs2d_ctx* ctx, const ViewSet& vs, const gs2d_track_args* a, 
       ba.order_pairs = ctx->placed;
       ba.order_scratch = reinterpret_cast<uint64_t*>(ctx->pairs);
       ba.order_ids = ctx->ids;
+      ba.order_tcount = ctx->tcount;
     }
     ProfScope ps(ctx, kBlendTrack, s);
     launch_blend_track(ba, ctx->opt.tile_w, ctx->opt.tile_h, work_ptr(ctx, s), s);

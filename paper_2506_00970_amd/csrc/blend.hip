@@ -896,9 +896,11 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(5))) voi
   uint32_t* const sid = reinterpret_cast<uint32_t*>(srec + a.batch * kRecF4);
   bool lds_list = false;
   if constexpr (NT == kBlockThreads) {
-    if (a.order_pairs)
+    if (a.order_pairs) {
+      if (t == 0) a.order_tcount[(size_t)tile * kCountStride] = 0u;
       lds_list = order_list(a.order_pairs, a.order_scratch, a.order_ids, start, end - start,
                             reinterpret_cast<uint64_t*>(srec), sid, false);
+    }
   }
   FwdPix s{1.0f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0, !inside};
   float Q[6], Ar[6], Ag[6], Ab[6], AD[6];

@@ -274,17 +274,19 @@ void launch_duplicate(const uint32_t* count, const uint32_t* part_pairs, const u
                       const uint2* rect, const ViewDesc* views, int n_views, int64_t items, int64_t p_cap,
                       const uint32_t* dkey, uint4* pairs, uint32_t* tcount, int n_tiles, Ctrl* ctrl,
                       uint32_t* np_host, hipStream_t s);
-// The tile ranges (empty after an overflow) from the counters, which are zero again
-// afterwards; with `order` (nullable) also the tiles by descending list length (counting
-// order over 64 buckets of 32 entries; within a bucket any order).
-void launch_ranges(uint32_t* tcount, int n_tiles, Ctrl* ctrl, uint2* ranges, uint32_t* order, hipStream_t s);
-// The pairs as (depth key << 32 | item) in their tiles' ranges, in any order within each.
-void launch_place(const uint4* pairs, Ctrl* ctrl, int64_t p_cap, const uint2* ranges, int n_tiles, uint64_t* placed,
-                  hipStream_t s);
+// Up to this many tiles the ranges and the placement are one launch.
+constexpr int kFusedTiles = 2048;
+// The tile ranges (empty after an overflow) from the counters, and the pairs as (depth key
+// << 32 | item) in their tiles' ranges, in any order within each; with `order` (nullable)
+// also the tiles by descending list length (counting order over 64 buckets of 32 entries;
+// within a bucket any order).
+void launch_ranges_place(const uint32_t* tcount, int n_tiles, const uint4* pairs, Ctrl* ctrl, int64_t p_cap,
+                         uint2* ranges, uint32_t* order, uint64_t* placed, hipStream_t s);
 // Orders every tile's pairs by (depth key, item) into ids; placed and scratch (of the
-// same size, for lists longer than one workgroup's LDS) are overwritten.
+// same size, for lists longer than one workgroup's LDS) are overwritten.  Zeroes the tile
+// counters (as the tracking walk does when it orders the lists).
 void launch_tile_order(const uint2* ranges, int n_tiles, uint64_t* placed, uint64_t* scratch, uint32_t* ids,
-                       hipStream_t s);
+                       uint32_t* tcount, hipStream_t s);
 // The tile keys and items of n pairs as emitted.
 void launch_split_pairs(const uint4* pairs, int64_t n, uint32_t* key, uint32_t* id, hipStream_t s);
 
@@ -327,6 +329,7 @@ struct BlendArgs {
   uint64_t* order_pairs = nullptr;
   uint64_t* order_scratch = nullptr;
   uint32_t* order_ids = nullptr;
+  uint32_t* order_tcount = nullptr;  // the tile counters, zeroed by the walk
   // forward and backward blends of many more tiles than fit on the GPU at once: workgroup
   // i blends tile order[i] (descending list length); null: by tile_stride
   const uint32_t* order = nullptr;
