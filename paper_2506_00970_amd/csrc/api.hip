@@ -235,7 +235,7 @@ int build_views(gs2d_ctx* ctx, const gs2d_view* in, int nv, ViewSet& vs) {
   return GS2D_OK;
 }
 
-// A stride near 97 that is coprime to n: the blend's workgroup -> tile map.
+// A stride near 97 that is coprime to n: the blend's workgroup -> tile group map.
 int tile_stride(int64_t n) {
   int s = 97;
   auto gcd = [](int64_t a, int64_t b) {
@@ -253,7 +253,7 @@ int tile_stride(int64_t n) {
 BlendArgs blend_args(gs2d_ctx* ctx, const ViewSet& vs) {
   BlendArgs a{ctx->ranges, ctx->ids, ctx->rec, ctx->views, vs.n_views,
               (int)vs.tiles, ctx->opt.z_near, ctx->opt.filter, ctx->opt.batch};
-  a.tile_stride = tile_stride(vs.tiles);
+  a.tile_stride = tile_stride((vs.tiles + kTileGroup - 1) / kTileGroup);
   a.order = ctx->order_on ? ctx->order : nullptr;
   a.check = &ctx->ctrl->check_bits;
   return a;

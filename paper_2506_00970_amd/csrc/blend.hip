@@ -116,12 +116,27 @@ __device__ __forceinline__ void prioritise(int len) {
 
 // The tile of a workgroup.  With an order (many more tiles than fit on the GPU at once):
 // the order's, longest lists first, so that the long lists start first and the short ones
-// fill in at the end.  Otherwise workgroups are dealt round-robin to the 8 XCDs, so each
-// XCD gets every 8th tile of the stride: an even share of the dense and sparse image
-// regions.
+// fill in at the end.  Otherwise the tiles go in groups of kTileGroup neighbours, which share
+// records, to one XCD (workgroups are dealt round-robin to the 8 XCDs, each with an L2 of
+// its own), and the XCD gets every 8th group of the stride: an even share of the dense and
+// sparse image regions.  Tracking walks of eight mixed rooms: 390 -> 371 and 356 -> 335 us
+// against single tiles by XCD, of one 640 x 480 view with 285k pairs 114 -> 109; groups of 8
+// and 16 measure the same.  n_tiles or more: a workgroup without a tile.
+constexpr int kXcds = 8;
+__device__ __forceinline__ int strided_tile(const BlendArgs& a) {
+  const uint32_t j = blockIdx.x / kXcds, groups = (uint32_t)(a.n_tiles + kTileGroup - 1) / kTileGroup;
+  const uint32_t g = j / kTileGroup * kXcds + blockIdx.x % kXcds;
+  if (g >= groups) return a.n_tiles;
+  return (int)((uint64_t)g * (uint64_t)a.tile_stride % groups) * kTileGroup + (int)(j % kTileGroup);
+}
+inline int strided_grid(const BlendArgs& a) {
+  if (a.order) return a.n_tiles;
+  const int groups = (a.n_tiles + kTileGroup - 1) / kTileGroup;
+  return (groups + kXcds - 1) / kXcds * kXcds * kTileGroup;
+}
 __device__ __forceinline__ int grid_tile(const BlendArgs& a) {
   if (a.order) return __builtin_amdgcn_readfirstlane((int)a.order[blockIdx.x]);
-  return (int)(((uint64_t)blockIdx.x * (uint64_t)a.tile_stride) % (uint64_t)a.n_tiles);
+  return strided_tile(a);
 }
 
 // The view of a global tile: lane k compares with view k's first tile, one load for the
@@ -521,7 +536,8 @@ __device__ __forceinline__ void blend_fwd_tile(const BlendArgs& a, const int til
 template <int TW, int TH, bool PROF>
 __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(TW * TH > 256 ? 8 : 6))) void blend_fwd_kernel(
     BlendArgs a, float* __restrict__ t_final, uint32_t* __restrict__ last_out, unsigned long long* __restrict__ work) {
-  blend_fwd_tile<TW, TH, PROF>(a, grid_tile(a), t_final, last_out, work);
+  const int tile = grid_tile(a);
+  if (tile < a.n_tiles) blend_fwd_tile<TW, TH, PROF>(a, tile, t_final, last_out, work);
 }
 
 // Per-pixel state of the backward walk.
@@ -844,7 +860,8 @@ template <int TW, int TH, bool POSE_ONLY, bool HAS_N, bool HAS_O, bool PROF>
 __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(4))) void blend_bwd_kernel(
     BlendArgs a, const float* __restrict__ t_final, const uint32_t* __restrict__ last_in, float* __restrict__ gacc,
     float* __restrict__ part, unsigned long long* __restrict__ work) {
-  blend_bwd_tile<TW, TH, POSE_ONLY, HAS_N, HAS_O, PROF>(a, grid_tile(a), t_final, last_in, gacc, part, work);
+  const int tile = grid_tile(a);
+  if (tile < a.n_tiles) blend_bwd_tile<TW, TH, POSE_ONLY, HAS_N, HAS_O, PROF>(a, tile, t_final, last_in, gacc, part, work);
 }
 
 // The tracking walk's LDS, in float4: the staged records, then the ordered list; before
@@ -874,7 +891,8 @@ __global__ __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(5))) voi
   extern __shared__ float4 srec[];
   __shared__ uint8_t s_list[NW][kMaxBatch];
   __shared__ float s_red[NW][8];
-  const int tile = (int)(((uint64_t)blockIdx.x * (uint64_t)a.tile_stride) % (uint64_t)a.n_tiles);
+  const int tile = strided_tile(a);
+  if (tile >= a.n_tiles) return;
   const ViewDesc& V = tile_view(a, tile);
   const CamF cam = V.cam;
   const int lt = tile - V.tile_base;
@@ -1063,10 +1081,10 @@ void fwd_shape(const BlendArgs& a, float* t_final, uint32_t* last, unsigned long
   const size_t lds = (size_t)a.batch * (kRecF4 * sizeof(float4) + (a.contrib ? sizeof(uint64_t) + sizeof(uint32_t) : 0));
   if (work) {
     auto k = blend_fwd_kernel<TW, TH, true>;
-    k<<<a.n_tiles, TW * TH, lds, s>>>(a, t_final, last, work);
+    k<<<strided_grid(a), TW * TH, lds, s>>>(a, t_final, last, work);
   } else {
     auto k = blend_fwd_kernel<TW, TH, false>;
-    k<<<a.n_tiles, TW * TH, lds, s>>>(a, t_final, last, work);
+    k<<<strided_grid(a), TW * TH, lds, s>>>(a, t_final, last, work);
   }
 }
 
@@ -1077,10 +1095,10 @@ void bwd_variant(const BlendArgs& a, const float* t_final, const uint32_t* last,
   const size_t lds = (size_t)a.batch * (kRecF4 * sizeof(float4) + (PO ? 0 : sizeof(uint32_t) + 16 * sizeof(double)));
   if (work) {
     auto k = blend_bwd_kernel<TW, TH, PO, HN, HO, true>;
-    k<<<a.n_tiles, TW * TH, lds, s>>>(a, t_final, last, gacc, part, work);
+    k<<<strided_grid(a), TW * TH, lds, s>>>(a, t_final, last, gacc, part, work);
   } else {
     auto k = blend_bwd_kernel<TW, TH, PO, HN, HO, false>;
-    k<<<a.n_tiles, TW * TH, lds, s>>>(a, t_final, last, gacc, part, work);
+    k<<<strided_grid(a), TW * TH, lds, s>>>(a, t_final, last, gacc, part, work);
   }
 }
 
@@ -1117,9 +1135,9 @@ template <int TW, int TH>
 void track_shape(const BlendArgs& a, unsigned long long* work, hipStream_t s) {
   const size_t lds = (size_t)track_lds_f4(a.batch) * sizeof(float4);
   if (work)
-    blend_track_kernel<TW, TH, true><<<a.n_tiles, TW * TH, lds, s>>>(a, work);
+    blend_track_kernel<TW, TH, true><<<strided_grid(a), TW * TH, lds, s>>>(a, work);
   else
-    blend_track_kernel<TW, TH, false><<<a.n_tiles, TW * TH, lds, s>>>(a, work);
+    blend_track_kernel<TW, TH, false><<<strided_grid(a), TW * TH, lds, s>>>(a, work);
 }
 
 void launch_blend_track(const BlendArgs& a, int tile_w, int tile_h, unsigned long long* work, hipStream_t s) {

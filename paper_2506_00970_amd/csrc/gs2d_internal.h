@@ -307,9 +307,9 @@ struct BlendArgs {
   float z_near;
   int filter;
   int batch;
-  // workgroup i blends tile (i * tile_stride) mod n_tiles (tile_stride coprime to
-  // n_tiles): neighbouring tiles, which have lists of similar length, start at
-  // different times and on different compute units
+  // group g of kTileGroup workgroups blends tile group (g * tile_stride) mod the number of
+  // groups (coprime to it): neighbouring groups, which have lists of similar length, start
+  // at different times and on different compute units
   int tile_stride = 1;
   // the tracking walk's tile rows (pose gradient in slots 0-5, loss in slot 6), and
   // the loss's depth weight and masks
@@ -337,6 +337,8 @@ struct BlendArgs {
   bool contrib = false;       // forward: some view has a contribution output
 };
 
+// Consecutive tiles that one XCD blends.
+constexpr int kTileGroup = 4;
 // Batched renders with more tiles than this take their tiles by descending list length.
 constexpr int kOrderMinTiles = 4096;
 // Tracking: forward blend, tracking loss and pose-only gradient in one walk; needs
