@@ -36,12 +36,12 @@ HBM_PEAK_GBS = 8000.0
 VALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 # VALU lane-op slots per unit of work, counted in the gfx950 code of the blend kernels
 # (transcendentals at 4 slots): per evaluated (pixel, surfel) pair (the pairs each pixel
-# walks before it terminates, after the per-wave cull) and per composited pair (3D
-# branch).  blend_track: the evaluation, then the compositing with the pose-gradient
-# terms; blend_fwd: the evaluation, then the 8-channel compositing; blend_bwd (all
-# parameters): the evaluation, then the reverse step and the 16 per-surfel terms it
-# adds (the wave reduction that carries those additions is not counted).
-OPS_PER_UNIT = {"blend_track": (45, 129), "blend_fwd": (43, 20), "blend_bwd": (42, 86)}
+# walks before it terminates, after the window test, whose own work is not counted) and per
+# composited pair (3D branch).  blend_track: the evaluation, then the compositing with the
+# pose-gradient terms; blend_fwd: the evaluation, then the 8-channel compositing; blend_bwd
+# (all parameters): the evaluation, then the reverse step and the 16 per-surfel terms it
+# adds (the group reduction that carries those additions is not counted).
+OPS_PER_UNIT = {"blend_track": (51, 133), "blend_fwd": (51, 20), "blend_bwd": (51, 92)}
 
 
 def log(msg):

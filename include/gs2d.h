@@ -89,8 +89,8 @@ typedef struct gs2d_options {
   int32_t keep_unsorted;     /* 1: keep a copy of the pairs before the tile sort (tests) */
   int32_t profile;           /* 1: time kernel families with HIP events and count blend work;
                                 2: time them only (the blend kernels then run the same code as
-                                without profiling); calls outside graph capture only; see
-                                gs2d_get_profile */
+                                without profiling); calls outside graph capture and tracking
+                                loops without use_graph only; see gs2d_get_profile */
 } gs2d_options;
 
 /* Counters of the last forward pass (gs2d_get_counts synchronises the stream). */
