@@ -35,8 +35,8 @@
 // against one entry per wave and step, 640 x 480 views of a 300k-surfel room with 80k
 // to 285k pairs: forward 33 -> 25 to 143 -> 86 us, with contributions 35 -> 27 to
 // 164 -> 80 us; full backward of five views 215 -> 187 to 274 -> 249 us; pose-only
-// backward of a 427 x 239 view 20 -> 17 to 72 -> 48 us; tracking walk 48 -> 35 to
-// 214 -> 121 us.
+// backward of a 427 x 239 view 20 -> 17 to 72 -> 48 us; tracking walk 48 -> 33 to
+// 214 -> 109 us (35 and 121 before the merge ordering and the tile groups).
 #include "tile_order.h"
 
 // The lane-write intrinsic, which has no builtin: `old` with lane `lane` replaced by the
